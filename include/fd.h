@@ -129,20 +129,24 @@ int fd_set_kchunk(int32_t kchunk);
 
 /* Performance knob: tile shape of the forward stencil kernels (fd_step,
  * fd_step_fused, fd_step_exchange, fd_forward_run, fd_adjoint_step_scaled):
- * 0 = automatic: a forward update that takes no faces inside the kernel --
- * fd_step, fd_step_fused, fd_forward_run without a second face set,
+ * 0 = automatic: grids of more than 2^18 and at most 12.5 million points, whose
+ * arrays stay in cache between steps, run as bricks (fd_step_bricks tells which):
+ * forward updates, fd_step_exchange / fd_forward_run with all twelve face buffers
+ * (nx a multiple of 4; the faces then read and written in that one launch), and
+ * gradient passes (of smaller grids too); strides, origin and buffers 16-byte
+ * aligned.  Where bricks do not apply: a forward update that takes no faces inside
+ * the kernel -- fd_step, fd_step_fused, fd_forward_run without a second face set,
  * fd_adjoint_step_scaled(_res) -- runs one thread per point on grids of at most
- * 2^22 points, which stay in cache and whose step is latency-bound, and so does
- * fd_step_exchange / fd_forward_run with all twelve face buffers on grids of at
- * most 2^21 points, the faces then read and written in that one launch; grids of
- * at least 7.5 million points take the kernel of 16-byte lanes (the exchange form
+ * 2^22 points, and so does fd_step_exchange / fd_forward_run with all twelve face
+ * buffers on grids of at most 2^21 points, the faces then read and written in that
+ * one launch; grids of at least 7.5 million points take the kernel of 16-byte lanes (the exchange form
  * where nx is a multiple of 128, with 128 x 32 tiles; the update without faces and
  * the gradient pass with 128 x 32 tiles, or 64 x 64 where the launch model prefers
  * them by a tenth, i.e. where a 128-wide tile column would be mostly empty; arrays
  * and face buffers 16-byte aligned); the others the z-marching kernel of one float
  * per lane, 64 x 16 tiles for grids of at most 2^20 points, 64 x 32 above.  1 =
- * always 64 x 32, 2 = always 64 x 16 (both: never one thread per point nor 16-byte
- * lanes), 3 = one thread per point wherever it applies (64 x 16 elsewhere), 4 =
+ * always 64 x 32, 2 = always 64 x 16 (both: never one thread per point, bricks nor
+ * 16-byte lanes), 3 = one thread per point wherever it applies (64 x 16 elsewhere), 4 =
  * 16-byte lanes wherever they apply, 128 x 32 tiles (64 x 32 elsewhere), 5 = the
  * same with 64 x 64 tiles where the 16-byte-lane kernel takes no faces.
  * Process-wide; results do not depend on it (fd_step_kernel reports the choice).
@@ -156,8 +160,9 @@ int fd_set_tiles(int32_t mode);
  * fd_set_tiles).  Host only, no device call; FD_EINVAL for a bad grid or NULL out. */
 int fd_step_launch(const fd_grid* g, int32_t out[4]);
 
-/* Which forward kernel a step over g takes, as the next call would choose it
- * (process-wide fd_set_tiles mode included; volume arrays and face buffers
+/* Which forward kernel a step over g takes where it does not run as bricks
+ * (fd_step_bricks == 0, or arrays that bricks cannot take), as the next call would
+ * choose it (process-wide fd_set_tiles mode included; volume arrays and face buffers
  * assumed 16-byte aligned, as torch allocates them): with_faces != 0 for
  * fd_step_exchange / fd_forward_run with all twelve face buffers, 0 for fd_step /
  * fd_step_fused / fd_forward_run without faces (no receiver row in the kernel).
@@ -173,6 +178,10 @@ enum {
   FD_KERNEL_WIDE_64x64 = 4    /* the same with 64 x 64 tiles (ragged x extents) */
 };
 int fd_step_kernel(const fd_grid* g, int32_t with_faces, int32_t out[6]);
+/* 1 if a step over g (with_faces as for fd_step_kernel, arrays and buffers 16-byte
+ * aligned) runs as bricks, 0 if fd_step_kernel's kernel steps it; FD_EINVAL for a bad
+ * grid.  Host only. */
+int fd_step_bricks(const fd_grid* g, int32_t with_faces);
 
 /* ----------------------------------------------------------- model prep
  * (set-up, step S0; not on the per-step path).  The paper names the acoustic
@@ -273,9 +282,9 @@ int fd_step_fused(const fd_grid* g, const float* u_prev, const float* u, float* 
  * multiple of 64 and all four x-face buffers are given, the x faces are
  * exchanged inside the stencil kernel (their 16-byte row pieces would otherwise
  * cost whole cache lines in a separate pack and unpack); the y and z faces,
- * whole rows and planes, go through the unpack and pack kernels.  On grids of at
- * most 2^21 points with all twelve face buffers given, the whole step is one
- * launch of the one-thread-per-point kernel (see fd_set_tiles).  On return u's
+ * whole rows and planes, go through the unpack and pack kernels.  On grids that run
+ * as bricks, or one thread per point, with all twelve face buffers given, the whole
+ * step is one launch (see fd_set_tiles).  On return u's
  * face halos are unspecified (they may hold the face_in values).  face_in
  * buffers must not overlap face_out buffers or any volume array (a real
  * exchange double-buffers them: the loopback passes the faces of the previous
@@ -304,9 +313,10 @@ int fd_step_exchange(const fd_grid* g, const float* u_prev, float* u, float* u_n
  * host array of nt floats, read before the call returns; traces is a device
  * array of nt*nrec floats (may be NULL when nt == 0); rec_off device int64
  * offsets (needed whenever nrec > 0).  With rec_map set, a step without faces
- * over a grid of at most 2^20 points, or one that runs the one-thread-per-point
- * kernel (see fd_set_tiles), takes its receiver row in the stencil launch; with
- * faces the row is taken in the pack launch, otherwise in a launch of its own.
+ * over a grid of at most 2^20 points, or one that runs as bricks, one thread per
+ * point or on 16-byte lanes (see fd_set_tiles), takes its receiver row in the stencil
+ * launch; with faces the row is taken in the pack launch (or in the stencil launch,
+ * where that is the whole step), otherwise in a launch of its own.
  * Same bits either way. */
 typedef struct fd_run {
   float* u_prev;

@@ -390,13 +390,20 @@ KERNEL_NAMES = {0: "point", 1: "march_64x32", 2: "march_64x16", 3: "wide_128x32"
 
 
 def step_kernel(grid: Grid, faces: bool = False) -> dict:
-    """The forward kernel a step over ``grid`` takes (fd_step_kernel): ``faces`` for the
-    exchange step with all twelve face buffers, else the update without faces."""
+    """The forward kernel a step over ``grid`` takes where it does not run as bricks
+    (fd_step_kernel; see ``step_bricks``): ``faces`` for the exchange step with all twelve
+    face buffers, else the update without faces."""
     out = (C.c_int32 * 6)()
     check(lib().fd_step_kernel(grid.ref, int(bool(faces)), out), "fd_step_kernel")
     kind, tx, ty, kc, zc, nb = out
     return {"kernel": KERNEL_NAMES[kind], "tile": (tx, ty), "kchunk": kc, "zchunks": zc,
             "blocks": nb}
+
+
+def step_bricks(grid: Grid, faces: bool = False) -> bool:
+    """Whether a step over ``grid`` runs as bricks (fd_step_bricks): the grids that the
+    caches hold between steps."""
+    return bool(check(lib().fd_step_bricks(grid.ref, int(bool(faces))), "fd_step_bricks"))
 
 
 # ----------------------------------------------------------------- forward model

@@ -99,13 +99,15 @@ bool overlaps(const fd_grid* g, const float* a, const float* b) {
   return a < b + n && b < a + n;
 }
 
-// The forward update with no faces inside the kernel: the one-thread-per-point
+// The forward update with no faces inside the kernel: bricks or the one-thread-per-point
 // kernel on grids small enough to stay in cache, else the z-marching kernel (the
-// same bits either way).
+// same bits whichever runs).
 hipError_t forward_update(const Geo& geo, const Coef& c, const float* up, const float* u,
                           float* un, const float* q, const float* ex, const float* ey,
                           const float* ez, const fd_source* src, hipStream_t s,
                           const RecPlane* rp = nullptr) {
+  const float* const arrs[4] = {up, u, un, q};
+  if (brick_takes(geo, arrs)) return launch_brick(geo, c, up, u, un, q, ex, ey, ez, src, rp, s);
   if (point_kernel_pays(geo)) return launch_step_point(geo, c, up, u, un, q, ex, ey, ez, src, rp, s);
   return launch_step(geo, c, up, u, un, q, ex, ey, ez, src, s, rp);
 }
@@ -257,6 +259,14 @@ int fd_step_kernel(const fd_grid* g, int32_t with_faces, int32_t out[6]) {
     out[5] = o[0] * o[1] * o[3];
   }
   return FD_OK;
+}
+
+int fd_step_bricks(const fd_grid* g, int32_t with_faces) {
+  int rc = check_grid(g);
+  if (rc) return rc;
+  const Geo geo = make_geo(g);
+  return brick_grid(geo) && (long long)geo.nx * geo.ny * geo.nz > kBrickLeastPoints &&
+         (!with_faces || (geo.nx % 4 == 0 && geo.ny >= 4 && geo.nz >= 4));
 }
 
 namespace {
@@ -464,8 +474,8 @@ static bool face_sets_overlap(const fd_grid* g, const float* const a[6], const f
 
 // One step of the exchange form, arguments already checked; with receivers
 // (nrec > 0) the receiver row of un is taken in the launch that packs its faces,
-// or, on grids that run one thread per point with all twelve faces, in that one
-// launch (with a plane map, rec_map) or one of its own.
+// or, on grids that run as bricks or one thread per point with all twelve faces, in
+// that one launch (with a plane map, rec_map) or one of its own.
 static hipError_t step_exchange(const Geo& geo, const Coef& c, const float* up, float* u,
                                 float* un, const float* q, const float* ex, const float* ey,
                                 const float* ez, const fd_source* src,
@@ -474,13 +484,19 @@ static hipError_t step_exchange(const Geo& geo, const Coef& c, const float* up, 
                                 float* row = nullptr, const int32_t* rec_map = nullptr,
                                 int rec_k = -1) {
   hipError_t e = hipSuccess;
-  bool all12 = face_in && face_out && point_exchange_pays(geo);
+  bool all12 = face_in && face_out;
   for (int f = 0; f < 6 && all12; ++f) all12 = face_in[f] && face_out[f];
-  if (all12) {  // small grid: the whole step in one launch
+  const float* const arrs[4] = {up, u, un, q};
+  const bool bricks = all12 && brick_takes(geo, arrs, face_in, face_out);
+  if (bricks || (all12 && point_exchange_pays(geo))) {  // the whole step in one launch
     const RecPlane rp{rec_map, rec_k, row};
     const bool in_kernel = rec_map && nrec > 0;
-    e = launch_step_point(geo, c, up, u, un, q, ex, ey, ez, src, in_kernel ? &rp : nullptr, s,
-                          face_in, face_out);
+    if (bricks)
+      e = launch_brick(geo, c, up, u, un, q, ex, ey, ez, src, in_kernel ? &rp : nullptr, s,
+                       face_in, face_out);
+    else
+      e = launch_step_point(geo, c, up, u, un, q, ex, ey, ez, src, in_kernel ? &rp : nullptr, s,
+                            face_in, face_out);
     if (e == hipSuccess && nrec > 0 && !in_kernel) e = launch_record(un, rec_off, nrec, row, s);
     return e;
   }
@@ -630,11 +646,11 @@ static hipError_t forward_steps(const fd_grid* g, fd_run* run, int nsend, int ns
       const RecPlane rp{run->rec_map, run->rec_k, row};
       // the one-thread-per-point kernel takes the row at the cost of one map load
       // per thread of the plane (128^3, sponge: 12.6 -> 10.1 us per step); the
-      // 16-byte-lane kernel loads its map entries before it marches
+      // 16-byte-lane kernel and the bricks load their map entries with the rest
       const float* const arrs[4] = {up, u, un, run->vdt2};
       const bool in_kernel = run->rec_map && run->nrec > 0 && !nsend &&
                              (receiver_plane_pays(geo) || point_kernel_pays(geo) ||
-                              wide_takes_step(geo, arrs));
+                              brick_takes(geo, arrs) || wide_takes_step(geo, arrs));
       if (nsend) e = launch_unpack(geo, u, recv, s);
       if (e == hipSuccess)
         e = forward_update(geo, c, up, u, un, run->vdt2, ex, ey, ez, sp_src, s,

@@ -165,6 +165,31 @@ bool wide_takes_step(const Geo& g, const float* const arrays[4]);
 hipError_t launch_grad_wide(const Geo& g, const Coef& c, const float* u, const float* an1,
                             float* gq, const float* ex, const float* ey, const float* ez,
                             const fd_source* src, hipStream_t s);
+// Grids that the caches hold, stepped as bricks (fd_brick.hip; same bits): more than
+// kBrickLeastPoints interior points (below that one thread per point finishes first: 64^3
+// 3.50 us against 3.47, with the faces exchanged 4.93 against 5.22) and at most
+// kBrickPoints, 200 MB of the 16 bytes per point that a step moves (224^3, 11.2M points:
+// 30.9 us against 37.7 of the marching kernel; 256 x 256 x 200, 13.1M: 43.9 against 41.3).
+constexpr long long kBrickLeastPoints = 1LL << 18;
+constexpr long long kBrickPoints = 12500000;
+// Whether bricks can step g at all: tile mode 0, at most kBrickPoints points, strides
+// and origin multiples of 4 floats, extents that fill the bricks.
+bool brick_grid(const Geo& g);
+// Whether a forward step over g with these arrays (u_prev, u, u_next, vdt2) takes the
+// brick kernel; with in and out (six receive and six send buffers) in the exchange
+// form: all twelve given, 16-byte aligned, nx a multiple of 4.
+bool brick_takes(const Geo& g, const float* const arrays[4], const float* const* in = nullptr,
+                 float* const* out = nullptr);
+// launch_step_point by the brick kernel, where brick_takes.
+hipError_t launch_brick(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
+                        const float* q, const float* ex, const float* ey, const float* ez,
+                        const fd_source* src, const RecPlane* rp, hipStream_t s,
+                        const float* const* in = nullptr, float* const* out = nullptr);
+// launch_grad by the brick kernel, where brick_grid and an1, u and gq are 16-byte
+// aligned; gq is read and written in place.
+hipError_t launch_grad_brick(const Geo& g, const Coef& c, const float* u, const float* an1,
+                             float* gq, const float* ex, const float* ey, const float* ez,
+                             const fd_source* src, hipStream_t s);
 // Whether a z-marching step over g takes its receiver row in the stencil launch
 // (small grids, whose launches are short) rather than in a launch of its own.
 bool receiver_plane_pays(const Geo& g);
@@ -193,6 +218,10 @@ struct WideStep {
   RecPlane rec{nullptr, -1, nullptr};  // receiver row written by the launch (map NULL: none)
 };
 hipError_t launch_wide_multi(const WideStep* steps, int n, hipStream_t s);
+// One step of up to kBrickMulti grids (each brick_grid, arrays 16-byte aligned, sponge
+// tables given) in one launch of bricks; same bits.
+constexpr int kBrickMulti = 16;
+hipError_t launch_brick_multi(const WideStep* steps, int n, hipStream_t s);
 // One time step of every shot listed in the tile table, by the 16-byte-lane kernel
 // (same bits as the other kernels; no receiver row in the kernel).
 hipError_t launch_batched4(const BatchShot* shots, const int4* tiles, int ntiles,

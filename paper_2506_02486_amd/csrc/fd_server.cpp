@@ -22,12 +22,13 @@
 // while more shots wait; else the caller's cap): a grid that fills the device runs
 // alone, grids that are small together share it.
 // A batched step advances every active shot by one launch: a lone shot by the
-// kernel its grid takes alone; several, if one of them is a grid of at least 7.5M
-// points, all by the 16-byte-lane kernel (up to kWideMulti grids with their
+// kernel its grid takes alone; several that the caches hold together as bricks (up to
+// kBrickMulti grids a launch, with their parameters in the kernel arguments); else, if
+// one of them is a grid of at least 7.5M points, all by the 16-byte-lane kernel (up to kWideMulti grids with their
 // parameters in the kernel arguments, each in 128 x 32 tiles or, where those would
 // leave a tenth more of its plane empty, 64 x 64; more through a tile table of
 // 128 x 32 tiles), else by the
-// one-float-per-lane kernel over a tile table (64 x 32 tiles).  Both write the trace
+// one-float-per-lane kernel over a tile table (64 x 32 tiles).  All write the trace
 // rows of shots whose receivers share one plane; one batched receiver launch takes
 // the others.
 // At most kEventEvery * kInflight steps are queued ahead of the device.  The arena,
@@ -221,6 +222,9 @@ struct Server {
   // 2..kWideMulti shots of the 16-byte-lane family: one launch with their parameters
   // in the kernel arguments (no tile table, no per-block look-up)
   std::vector<Shot*> multi;
+  // all active shots, where two or more run and the caches hold their grids together:
+  // stepped as bricks, kBrickMulti of them a launch
+  std::vector<Shot*> bricks;
   bool table_dirty = false;
   // shared state
   std::mutex mu;
@@ -460,11 +464,21 @@ hipError_t upload_tables(Server* S) {
   // else by the one-float-per-lane kernels
   bool any_wide = false;
   for (const Shot* s : S->slots) any_wide = any_wide || (s && s->wide);
+  // several grids that the caches hold together are stepped as bricks instead,
+  // kBrickMulti of them a launch
+  S->bricks.clear();
+  bool all_bricks = points_in_use(S) <= kBrickPoints;
+  for (Shot* s : S->slots)
+    if (s) {
+      S->bricks.push_back(s);
+      all_bricks = all_bricks && brick_grid(s->geo);
+    }
+  if (!all_bricks || S->bricks.size() < 2) S->bricks.clear();
   for (Shot* s : S->slots)
     if (s) s->in_wide = any_wide;
   for (int f = 0; f < 2; ++f) S->direct[f] = nullptr;
   for (Shot* s : S->slots)
-    if (s) {
+    if (s && S->bricks.empty()) {
       ++fam[s->in_wide ? 1 : 0];
       S->direct[s->in_wide ? 1 : 0] = s;
     }
@@ -477,10 +491,11 @@ hipError_t upload_tables(Server* S) {
     S->direct_rows[f] = false;
     if (const Shot* s = S->direct[f])  // as fd_forward_run samples a lone grid
       S->direct_rows[f] = s->plane_k >= 0 &&
-                          (f == 1 || point_kernel_pays(s->geo) || receiver_plane_pays(s->geo));
+                          (f == 1 || point_kernel_pays(s->geo) || receiver_plane_pays(s->geo) ||
+                           brick_grid(s->geo));
   }
   for (const Shot* s : S->slots)
-    if (s && s != S->direct[s->in_wide ? 1 : 0] && !(s->in_wide && !S->multi.empty())) {
+    if (s && S->bricks.empty() && s != S->direct[s->in_wide ? 1 : 0] && !(s->in_wide && !S->multi.empty())) {
       const int f = s->in_wide ? 1 : 0;
       xy[f].push_back((long long)((s->d.nx + tws[f][0] - 1) / tws[f][0]) *
                       ((s->d.ny + tws[f][1] - 1) / tws[f][1]));
@@ -510,7 +525,7 @@ hipError_t upload_tables(Server* S) {
         h_slots[na++] = slot;
         mr = std::max(mr, s->d.nrec);
       }
-      if (s == S->direct[f] || (f == 1 && !S->multi.empty())) continue;
+      if (!S->bricks.empty() || s == S->direct[f] || (f == 1 && !S->multi.empty())) continue;
       const int bxn = (s->d.nx + tws[f][0] - 1) / tws[f][0];
       const int byn = (s->d.ny + tws[f][1] - 1) / tws[f][1];
       const int bzn = (s->d.nz + kc[f] - 1) / kc[f];
@@ -540,7 +555,7 @@ hipError_t upload_tables(Server* S) {
 }
 
 // One step of a lone shot of its family by the single-grid launch (as fd_forward_run
-// steps it: the one-thread-per-point kernel on small grids, the marching kernels
+// steps it: one thread per point or bricks on small grids, the marching kernels
 // above; with `rows` the receiver row is written by the same launch).
 hipError_t step_direct(Server* S, Shot* s, bool rows) {
   const int n = s->n;
@@ -561,6 +576,10 @@ hipError_t step_direct(Server* S, Shot* s, bool rows) {
   const float* up = arr[(n + 2) % 3];
   const float* u = arr[n % 3];
   float* un = arr[(n + 1) % 3];
+  const float* const arrs[4] = {up, u, un, q};
+  if (brick_takes(s->geo, arrs))
+    return launch_brick(s->geo, s->coef, up, u, un, q, ex, ey, ez, &src, rows ? &rp : nullptr,
+                        S->cs);
   if (s->in_wide)
     return launch_forward_wide(s->geo, s->coef, up, u, un, q, ex, ey, ez, &src, nullptr, nullptr,
                                S->cs, rows ? &rp : nullptr);
@@ -570,12 +589,18 @@ hipError_t step_direct(Server* S, Shot* s, bool rows) {
   return launch_step(s->geo, s->coef, up, u, un, q, ex, ey, ez, &src, S->cs, rows ? &rp : nullptr);
 }
 
-// One step of the 16-byte-lane family's shots in one launch, their parameters in the
-// kernel arguments.
-hipError_t step_multi(Server* S) {
-  WideStep w[kWideMulti];
+// One step of the given shots by launches of up to `most` grids, their parameters in
+// the kernel arguments: 16-byte lanes (launch_wide_multi) or bricks.
+hipError_t step_multi(Server* S, const std::vector<Shot*>& shots, int most,
+                      hipError_t (*launch)(const WideStep*, int, hipStream_t)) {
+  WideStep w[std::max(kWideMulti, kBrickMulti)];
   int n = 0;
-  for (Shot* s : S->multi) {
+  for (Shot* s : shots) {
+    if (n == most) {
+      const hipError_t e = launch(w, n, S->cs);
+      if (e != hipSuccess) return e;
+      n = 0;
+    }
     const int k = s->n;
     float* arr[3];
     for (int i = 0; i < 3; ++i) arr[i] = shot_vol(S, s, i);
@@ -591,12 +616,13 @@ hipError_t step_multi(Server* S) {
     x.ey = sp + s->d.nx;
     x.ez = sp + s->d.nx + s->d.ny;
     x.src = fd_source{s->d.src[0], s->d.src[1], s->d.src[2], s->w[k]};
+    x.rec = RecPlane{nullptr, -1, nullptr};
     if (s->plane_k >= 0)
       x.rec = RecPlane{reinterpret_cast<const int32_t*>(shot_at(S, s, s->L.rmap)), s->plane_k,
                        reinterpret_cast<float*>(shot_at(S, s, s->L.traces)) +
                            (size_t)k * s->d.nrec};
   }
-  return launch_wide_multi(w, n, S->cs);
+  return launch(w, n, S->cs);
 }
 
 // Release a shot's block and admission resources (nothing of the shot's may still
@@ -821,13 +847,15 @@ void progress(Server* S) {
     if (step % kEventEvery == 0 && grp >= kInflight)
       e = hipEventSynchronize(S->step_ev[grp % kInflight]);
     if (e == hipSuccess && dirty) e = upload_tables(S);
+    if (e == hipSuccess && !S->bricks.empty())
+      e = step_multi(S, S->bricks, kBrickMulti, launch_brick_multi);
     for (int f = 0; f < 2 && e == hipSuccess; ++f) {
       if (Shot* s = S->direct[f]) {
         e = step_direct(S, s, S->direct_rows[f]);
       } else if (f == 0) {
         e = launch_batched(S->d_shots, S->d_tiles, S->ntiles, a, S->cs);
       } else if (!S->multi.empty()) {
-        e = step_multi(S);
+        e = step_multi(S, S->multi, kWideMulti, launch_wide_multi);
       } else {
         e = launch_batched4(S->d_shots, S->d_tiles + S->ntiles, S->ntiles4, a, S->cs);
       }

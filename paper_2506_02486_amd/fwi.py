@@ -35,9 +35,9 @@ from . import api
 
 # grids up to this many points run short, latency-bound launches: there the receiver
 # residual is added in the adjoint update's own launch (fd_adjoint_step_scaled_res),
-# as it is on grids the 16-byte-lane kernel steps (it loads the residual row before it
-# marches); the marching kernel of one float per lane in between would wait for its
-# map lookup, and a separate launch costs less there
+# as it is on grids that run as bricks or on 16-byte lanes (they load the residual row
+# with their other operands); the marching kernel of one float per lane would wait for
+# its map lookup, and a separate launch costs less there
 SMALL_GRID_POINTS = 1 << 20
 
 
@@ -197,7 +197,7 @@ class FWIProblem:
         g = self.grid
         if self.rec_plane is None:
             return False
-        return (g.nx * g.ny * g.nz <= SMALL_GRID_POINTS
+        return (g.nx * g.ny * g.nz <= SMALL_GRID_POINTS or api.step_bricks(g)
                 or api.step_kernel(g)["kernel"] in ("wide_128x32", "wide_64x64"))
 
     def _backward_scaled(self, res: torch.Tensor, want_grad_w: bool):
