@@ -7,21 +7,47 @@
 // FP64 matrix cores (v_mfma_f64_16x16x4f64): the paper states no element type,
 // and FP64 is the precision of the oracle that defines the product.
 //
-// Block: 1024 threads (16 waves), a 256 x 128 tile of C; each wave owns a 32 x 64
-// piece as 2 x 4 MFMA tiles of 16 x 16 (8 independent accumulators of 4 doubles per
-// lane), so that four waves share each SIMD and one's LDS and barrier phases hide
-// behind the others' MFMAs.  The K loop takes 16 columns of A and 16 rows of B per stage, staged in
-// double-buffered LDS; the next stage is loaded into registers while the MFMAs of the
-// current one run.
-// Operands of any shape and leading dimension: K is split into a first stage of
-// 1..16 columns, whose loads past K read 0, and whole stages, whose loads need no
-// bounds arithmetic (a pointer per thread plus the stage's offset); rows past m and
-// columns past n are read clamped and their results not stored.  Blocks sharing a B
-// panel (a column of tiles) run on one XCD in succession, so that the panel is read
-// from HBM about once.
+// Large products (gemm_f64_kernel).  Block: 1024 threads (16 waves), a 256 x 128 tile
+// of C; each wave owns a 32 x 64 piece as 2 x 4 MFMA tiles of 16 x 16 (8 independent
+// accumulators of 4 doubles per lane), so that four waves share each SIMD.  The K loop
+// takes 16 columns of A and 16 rows of B per stage, staged in double-buffered LDS.  The
+// matrix cores bound it, and what kept them idle was that all waves of the block wrote a
+// stage to LDS, met at the barrier and read their first fragments at the same time
+// (MFMA utilisation 84.7%), so the non-MFMA work is spread between the MFMAs:
+//   * a stage is written to LDS in the middle of the MFMAs of the stage before it,
+//     from registers loaded one whole stage earlier;
+//   * fragments are double-buffered: each k-step's are read during the MFMAs of the
+//     one before, and the last k-step's MFMAs run after the barrier, while the first
+//     fragments of the next stage arrive;
+//   * LDS accesses and loads are issued one MFMA at a time (sched_group_barrier).
+// 3780 x 30240 x 3780: 65.3 -> 67.4-68.1 TFLOP/s; 8192^3: 68.2 -> 70.3-71.0 (vendor BLAS 72.1 on
+// the same box).  Writing a stage earlier alone gave nothing (64.4), with the double
+// fragments 67.4.
+//
+// Smaller products (gemm_pair_kernel) leave most CUs idle with 256 x 128 tiles (512 x
+// 4096 x 512, one of Cannon's products at N = 4096 and P = 8: 64 tiles on 256 CUs), so
+// they take 128 x 128, 64 x 64 or 32 x 64 tiles, whichever the cost model below
+// (gemm_tile) prices lowest.  Their waves own 32 x 32, 16 x 32 or 16 x 16 pieces, for
+// which fragment reads of single doubles would bound the kernel (58 of LDS's 128 bytes
+// per clock at 64 x 64, as 8-byte reads): K is kept in pairs in LDS (A [m][k], B [k/2][n]
+// [2]) and a lane reads two k-steps with one 16-byte access, step h of a pair taking k =
+// 8 p + 2 (lane / 16) + h (any order of k will do as long as A and B agree).  The
+// elements of C to add to are read before the K loop.  Same pipelining otherwise.
+// Measured (us, before / after; before: 256 x 128 tiles): 512 x 4096 x 512 140 / 40.7
+// (52.7 TFLOP/s), 1000 x 4000 x 1000 260 / 134, 1285 x 7710 x 1285 662 / 447, 700^3 184 /
+// 18.3, 256 x 2048 x 256 72 / 8.8, 52 x 260 x 52 26 / 7.7 (the launch rate of the loop
+// that timed it).
+//
+// Operands of any shape and leading dimension: K is split into a first stage of 1 to a
+// whole stage's columns, whose loads past K read 0, and whole stages, whose loads need no
+// bounds arithmetic (an offset per thread from the tile's base plus the stage's offset);
+// rows past m and columns past n are read clamped and their results not stored.  Blocks
+// sharing a B panel (a column of tiles) run on one XCD in succession, so that the panel
+// is read from HBM about once.
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "fd.h"
 #include "fd_internal.h"
@@ -30,6 +56,9 @@ namespace fd {
 namespace {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+// two consecutive doubles in memory, aligned as one
+typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
 
 constexpr int BM = 256;          // tile rows (M)
 constexpr int BN = 128;          // tile columns (N)
@@ -73,6 +102,9 @@ __device__ __forceinline__ int remap_gemm(int bid, int nb) {
   return bid;
 }
 
+// OFF: the type of an element's offset from its tile's base: 32 bits, or 64 where a
+// leading dimension is too large for that (gemm_offsets_fit).
+template <class OFF>
 __global__ void __launch_bounds__(GT, WAVES_PER_SIMD) gemm_f64_kernel(GemmArgs g) {
   __shared__ double sa[2][BM * SA];
   __shared__ double sb[2][BK * SB];
@@ -97,29 +129,35 @@ __global__ void __launch_bounds__(GT, WAVES_PER_SIMD) gemm_f64_kernel(GemmArgs g
   // whole stages of BK.  Rows of A past m and columns of B past n are read clamped and
   // not cleared: they only reach rows and columns of the tile that are not stored.
   // Only the first stage clears what lies past its kt columns (in both operands: 0 x
-  // Inf would be NaN).  So a load of a whole stage is a per-thread pointer plus the
-  // stage's uniform offset, with no bounds arithmetic, and every load is unconditional
+  // Inf would be NaN).  So a load of a whole stage is a per-thread offset from the
+  // stage's uniform base, with no bounds arithmetic, and every load is unconditional
   // (a load under a branch would make the compiler wait for it where the branch joins).
   const int64_t stages = (g.k + BK - 1) / BK;
   const int64_t kt = g.k - (stages - 1) * BK;
-  const double* pa[A_PER];
-  const double* pb[B_PER];
-  const int64_t bcol = std::min(n0 + bc, g.n - 1);
+  const double* At = g.a + m0 * g.lda;
+  const double* Bt = g.b + n0;
+  const int mr = (int)std::min<int64_t>(g.m - m0, BM) - 1;  // last row and column of C
+  const int nr = (int)std::min<int64_t>(g.n - n0, BN) - 1;  // in the tile
+  OFF oa[A_PER], ob[B_PER];
 #pragma unroll
   for (int i = 0; i < A_PER; ++i)  // (k < BK: a single stage, read clamped in K)
-    pa[i] = g.a + std::min(m0 + ar + (GT / BK) * i, g.m - 1) * g.lda +
-            std::min<int64_t>(ak, g.k - 1);
+    oa[i] = (OFF)std::min(ar + (GT / BK) * i, mr) * (OFF)g.lda +
+            (OFF)std::min<int64_t>(ak, g.k - 1);
 #pragma unroll
   for (int i = 0; i < B_PER; ++i)
-    pb[i] = g.b + std::min<int64_t>(br + (GT / BN) * i, g.k - 1) * g.ldb + bcol;
+    ob[i] = (OFF)std::min<int64_t>(br + (GT / BN) * i, g.k - 1) * (OFF)g.ldb +
+            (OFF)std::min(bc, nr);
   double ra[A_PER], rb[B_PER];
-  // whole stage at column k0 = kt + (s - 1) BK of A, row k0 of B (s >= 1)
-  auto load_stage = [&](int64_t k0) {
-    const int64_t boff = k0 * g.ldb;
+  // whole stage s >= 1 at column k0 = kt + (s - 1) BK of A, row k0 of B (past the last
+  // stage: that one again, into the buffer nobody reads)
+  auto load_stage = [&](int64_t s) {
+    const int64_t k0 = std::max<int64_t>(kt + (std::min(s, stages - 1) - 1) * BK, 0);
+    const double* Ak = At + k0;
+    const double* Bk = Bt + k0 * g.ldb;
 #pragma unroll
-    for (int i = 0; i < A_PER; ++i) ra[i] = pa[i][k0];
+    for (int i = 0; i < A_PER; ++i) ra[i] = Ak[oa[i]];
 #pragma unroll
-    for (int i = 0; i < B_PER; ++i) rb[i] = pb[i][boff];
+    for (int i = 0; i < B_PER; ++i) rb[i] = Bk[ob[i]];
   };
   auto store_stage = [&](int buf) {
 #pragma unroll
@@ -139,45 +177,72 @@ __global__ void __launch_bounds__(GT, WAVES_PER_SIMD) gemm_f64_kernel(GemmArgs g
     // (a cleared element reads the stage's last valid one, in bounds)
 #pragma unroll
     for (int i = 0; i < A_PER; ++i) {
-      const double x = g.a[std::min(m0 + ar + (GT / BK) * i, g.m - 1) * g.lda +
-                           std::min<int64_t>(ak, kt - 1)];
+      const double x = At[(int64_t)std::min(ar + (GT / BK) * i, mr) * g.lda +
+                          std::min<int64_t>(ak, kt - 1)];
       ra[i] = ak < kt ? x : 0.0;
     }
 #pragma unroll
     for (int i = 0; i < B_PER; ++i) {
       const int64_t row = br + (GT / BN) * i;
-      const double x = g.b[std::min(row, kt - 1) * g.ldb + bcol];
+      const double x = Bt[std::min(row, kt - 1) * g.ldb + std::min(bc, nr)];
       rb[i] = row < kt ? x : 0.0;
     }
     store_stage(0);
+    load_stage(1);
   }
   __syncthreads();
   // fragment lanes: A rows / B columns lane % 16 of a 16-wide tile, k = lane / 16
   const int fr = lane & 15;
   const int fk = lane >> 4;
+  const int fa = (wm + fr) * SA + fk;
+  const int fb = fk * SB + wn + fr;
+  double af[2][FM], bf[2][FN];
+  auto frags = [&](int set, int buf, int kk) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i) af[set][i] = sa[buf][fa + 16 * i * SA + kk];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) bf[set][j] = sb[buf][fb + kk * SB + 16 * j];
+  };
+  constexpr int NQ = BK / 4;
+  static_assert(NQ % 2 == 0, "the fragment sets alternate over a stage");
+  frags(0, 0, 0);
   for (int64_t s = 0; s < stages; ++s) {
     const int buf = (int)(s & 1);
-    // the next stage's loads, unconditional (the last iteration reloads its own
-    // stage into the buffer nobody reads again): a load under a branch would make
-    // the compiler wait for it where the branch joins, before the MFMAs
-    load_stage(std::max<int64_t>(kt + (std::min(s + 1, stages - 1) - 1) * BK, 0));
-    const double* A = sa[buf];
-    const double* B = sb[buf];
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      double af[FM], bf[FN];
-#pragma unroll
-      for (int i = 0; i < FM; ++i) af[i] = A[(wm + 16 * i + fr) * SA + kk + fk];
-#pragma unroll
-      for (int j = 0; j < FN; ++j) bf[j] = B[(kk + fk) * SB + wn + 16 * j + fr];
+    for (int q = 0; q < NQ; ++q) {
+      __builtin_amdgcn_sched_barrier(0);
+      // the next k-step's fragments; those of the next stage after the barrier, past
+      // which nobody reads this stage's buffer any more
+      if (q < NQ - 1) {
+        frags((q + 1) & 1, buf, 4 * (q + 1));
+      } else {
+        __syncthreads();
+        frags(0, buf ^ 1, 0);
+      }
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[i], bf[j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[q & 1][i], bf[q & 1][j], acc[i][j],
+                                                           0, 0, 0);
+      if (q == 0) {
+        store_stage(buf ^ 1);
+        load_stage(s + 2);
+      }
+      // issue order: one MFMA (0x8), then its share of the LDS reads (0x100) and, in
+      // the first k-step, of the LDS writes (0x200) and loads (0x20)
+      constexpr int NM = FM * FN, NR = FM + FN, NW = A_PER + B_PER;
+      static_assert(NR <= NM && NW <= NM, "at most one of each per MFMA");
+#pragma unroll
+      for (int z = 0; z < NM; ++z) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        if ((z + 1) * NR / NM != z * NR / NM) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        if (q == 0 && (z + 1) * NW / NM != z * NW / NM) {
+          __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+        }
+      }
     }
-    store_stage(buf ^ 1);
-    __syncthreads();
   }
 
   // accumulator element v of lane l holds row l / 16 + 4 v, column l % 16 of its
@@ -198,6 +263,212 @@ __global__ void __launch_bounds__(GT, WAVES_PER_SIMD) gemm_f64_kernel(GemmArgs g
       }
     }
 }
+
+// Tiles of PM x PN of waves of VM x VN, stages of PK columns; at most 16 waves per CU
+// (four per SIMD) in the register budget.
+template <int PM, int PN, int VM, int VN, int PK>
+__global__ void __launch_bounds__(64 * (PM / VM) * (PN / VN), WAVES_PER_SIMD)
+    gemm_pair_kernel(GemmArgs g) {
+  constexpr int WN = PN / VN;
+  constexpr int PT = 64 * (PM / VM) * WN;  // threads
+  constexpr int FI = VM / 16, FJ = VN / 16;
+  constexpr int KP = PK / 2;   // pairs of k per stage
+  constexpr int PA = PK + 2;   // LDS pitches: A row, B pair row (16-byte reads of 8 lanes
+  constexpr int PB = 2 * PN;   // fall on distinct banks)
+  constexpr int NA = PM * KP / PT, NB = KP * PN / PT;  // pairs a thread loads per stage
+  constexpr int NP = PK / 8;   // pairs of k-steps per stage
+  static_assert(NA * PT == PM * KP && NB * PT == KP * PN && NP % 2 == 0, "tile shape");
+  __shared__ __attribute__((aligned(16))) double sa[2][PM * PA];
+  __shared__ __attribute__((aligned(16))) double sb[2][KP * PB];
+
+  const int logical = remap_gemm(blockIdx.x, gridDim.x);
+  const int64_t m0 = (int64_t)(logical % g.tiles_m) * PM;
+  const int64_t n0 = (int64_t)(logical / g.tiles_m) * PN;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int wm = (w / WN) * VM, wn = (w % WN) * VN;
+  const int64_t stages = (g.k + PK - 1) / PK;  // k >= 1
+  const int64_t kt = g.k - (stages - 1) * PK;
+  const double* At = g.a + m0 * g.lda;
+  const double* Bt = g.b + n0;
+  const int mr = (int)std::min<int64_t>(g.m - m0, PM) - 1;
+  const int nr = (int)std::min<int64_t>(g.n - n0, PN) - 1;
+  // thread's pair i of A: row e / KP, pair e % KP; of B: pair row e / PN, column e % PN
+  unsigned oa[NA], ob[NB];
+  int la[NA], lb[NB];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    const int e = t + PT * i, row = e / KP, kp = e % KP;
+    oa[i] = (unsigned)std::min(row, mr) * (unsigned)g.lda + 2u * kp;
+    la[i] = row * PA + 2 * kp;
+  }
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int e = t + PT * i, kp = e / PN, col = e % PN;
+    ob[i] = 2u * kp * (unsigned)g.ldb + (unsigned)std::min(col, nr);
+    lb[i] = kp * PB + 2 * col;
+  }
+  d2 ra[NA], rb[NB];
+  auto load_stage = [&](int64_t s) {  // whole stage 1 <= s < stages
+    const int64_t k0 = kt + (s - 1) * PK;
+    const double* Ak = At + k0;
+    const double* Bk = Bt + k0 * g.ldb;
+#pragma unroll
+    for (int i = 0; i < NA; ++i) ra[i] = *reinterpret_cast<const d2u*>(Ak + oa[i]);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      rb[i][0] = Bk[ob[i]];
+      rb[i][1] = (Bk + g.ldb)[ob[i]];
+    }
+  };
+  auto store_stage = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) *reinterpret_cast<d2*>(&sa[buf][la[i]]) = ra[i];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) *reinterpret_cast<d2*>(&sb[buf][lb[i]]) = rb[i];
+  };
+  // the first stage: kt columns of A and rows of B, the rest 0
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    const int e = t + PT * i;
+    const double* row = At + (int64_t)std::min(e / KP, mr) * g.lda;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t k = 2 * (e % KP) + h;
+      const double x = row[std::min(k, kt - 1)];
+      ra[i][h] = k < kt ? x : 0.0;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int e = t + PT * i;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t k = 2 * (e / PN) + h;
+      const double x = Bt[std::min(k, kt - 1) * g.ldb + std::min(e % PN, nr)];
+      rb[i][h] = k < kt ? x : 0.0;
+    }
+  }
+  const int fr = lane & 15, fk = lane >> 4;
+  // C to add to (an element outside C reads the tile's last row or column)
+  double c0[FI][FJ][4];  // (set and used where g.accumulate)
+  if (g.accumulate) {
+#pragma unroll
+    for (int i = 0; i < FI; ++i)
+#pragma unroll
+      for (int j = 0; j < FJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          c0[i][j][v] = g.c[(m0 + std::min(wm + 16 * i + fk + 4 * v, mr)) * g.ldc + n0 +
+                            std::min(wn + 16 * j + fr, nr)];
+  }
+  d4 acc[FI][FJ];
+#pragma unroll
+  for (int i = 0; i < FI; ++i)
+#pragma unroll
+    for (int j = 0; j < FJ; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+  store_stage(0);
+  if (stages > 1) load_stage(1);
+  __syncthreads();
+  // fragments of a pair of k-steps: lane l holds k = 8 p + 2 (l / 16) + {0, 1} of row /
+  // column l % 16
+  const int fa = (wm + fr) * PA + 2 * fk, fb = fk * PB + 2 * (wn + fr);
+  d2 af[2][FI], bf[2][FJ];
+  auto frags = [&](int set, int buf, int p) {
+#pragma unroll
+    for (int i = 0; i < FI; ++i)
+      af[set][i] = *reinterpret_cast<const d2*>(&sa[buf][fa + 16 * i * PA + 8 * p]);
+#pragma unroll
+    for (int j = 0; j < FJ; ++j)
+      bf[set][j] = *reinterpret_cast<const d2*>(&sb[buf][fb + 4 * p * PB + 32 * j]);
+  };
+  auto mma = [&](int set) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < FI; ++i)
+#pragma unroll
+        for (int j = 0; j < FJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[set][i][h], bf[set][j][h],
+                                                           acc[i][j], 0, 0, 0);
+  };
+  frags(0, 0, 0);
+  for (int64_t s = 0; s + 1 < stages; ++s) {
+    const int buf = (int)(s & 1);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (q < NP - 1) {
+        frags((q + 1) & 1, buf, q + 1);
+      } else {  // past the barrier nobody reads this stage's buffer any more
+        __syncthreads();
+        frags(0, buf ^ 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      mma(q & 1);
+      if (q == 0) {
+        __builtin_amdgcn_sched_barrier(0);
+        store_stage(buf ^ 1);
+        load_stage(std::min(s + 2, stages - 1));
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NP; ++q) {
+    if (q < NP - 1) frags((q + 1) & 1, (int)((stages - 1) & 1), q + 1);
+    mma(q & 1);
+  }
+#pragma unroll
+  for (int i = 0; i < FI; ++i)
+#pragma unroll
+    for (int j = 0; j < FJ; ++j) {
+      const int col = wn + 16 * j + fr;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = wm + 16 * i + fk + 4 * v;
+        if (row <= mr && col <= nr) {
+          double* p = g.c + (m0 + row) * g.ldc + n0 + col;
+          *p = g.accumulate ? c0[i][j][v] + acc[i][j][v] : acc[i][j][v];
+        }
+      }
+    }
+}
+
+// The tile shapes, largest first.
+struct TileCost {
+  int m, n;
+  double busy;   // us a CU spends on one tile per 16 of K when it has several
+  double alone;  // the same for the last one, which shares its CU with no other
+};
+// From 2048 x 8192 x 2048 (every CU has several tiles) and, alone, from products with one
+// tile per CU (1000 x 4000 x 1000, 256 x 2048 x 256) or fewer.
+constexpr TileCost kTiles[4] = {{256, 128, 3.93, 4.15},
+                                {128, 128, 2.04, 2.09},
+                                {64, 64, 0.552, 0.69},
+                                {32, 64, 0.302, 0.40}};
+
+// The tile shape of least modelled time: the fullest CU's tiles, one after the other.
+// The model is within 8% of the measured time of every shape on 512 x 4096 x 512, 1285 x
+// 7710 x 1285, 2048 x 8192 x 2048 and 3780 x 30240 x 3780, so its choice is the fastest or
+// as good: 52.7 TFLOP/s (64 x 64; 30.5 with 128 x 128), 57.0 (64 x 64; 50.6), 68.2 (256 x
+// 128; 65.6) and 68.1 (256 x 128; 65.5).
+int gemm_tile(int64_t m, int64_t n) {
+  int best = 0;
+  double cost = -1.0;
+  for (int i = 0; i < 4; ++i) {
+    const double tiles = (double)((m + kTiles[i].m - 1) / kTiles[i].m) *
+                         (double)((n + kTiles[i].n - 1) / kTiles[i].n);
+    const double most = std::ceil(tiles / 256.0);
+    const double c = (most - 1.0) * kTiles[i].busy + kTiles[i].alone;
+    if (cost < 0.0 || c < cost) {
+      cost = c;
+      best = i;
+    }
+  }
+  return best;
+}
+
+// Offsets from a tile's base fit 32 bits: at most 256 rows of A or 32 of B.
+bool gemm_offsets_fit(int64_t lda, int64_t ldb) { return lda < (1LL << 23) && ldb < (1LL << 26); }
 
 // Last byte (exclusive) a row-major rows x cols operand with leading dimension ld
 // occupies, from its first element.
@@ -233,8 +504,12 @@ extern "C" int fd_block_gemm_f64(int64_t m, int64_t n, int64_t k, const double* 
         ranges_overlap(c, cb, b, extent_bytes(k, n, ldb)))
       return fail(FD_EINVAL, "fd_block_gemm_f64: c overlaps a or b");
   }
-  const int64_t tm = (m + BM - 1) / BM;
-  const int64_t tn = (n + BN - 1) / BN;
+  // (k == 0 only clears or keeps C, and large leading dimensions need 64-bit offsets:
+  // both by the first kernel)
+  const bool fits = gemm_offsets_fit(lda, ldb);
+  const int tile = k > 0 && fits ? gemm_tile(m, n) : 0;
+  const int64_t tm = (m + kTiles[tile].m - 1) / kTiles[tile].m;
+  const int64_t tn = (n + kTiles[tile].n - 1) / kTiles[tile].n;
   if (tm * tn > 0x7fffffffLL || tm > 0x7fffffffLL)
     return fail(FD_EINVAL, "fd_block_gemm_f64: too many tiles");
   GemmArgs g;
@@ -249,7 +524,15 @@ extern "C" int fd_block_gemm_f64(int64_t m, int64_t n, int64_t k, const double* 
   g.ldc = ldc;
   g.tiles_m = (int)tm;
   g.accumulate = accumulate ? 1 : 0;
-  hipLaunchKernelGGL(gemm_f64_kernel, dim3((unsigned)(tm * tn)), dim3(GT), 0,
-                     reinterpret_cast<hipStream_t>(stream), g);
+  const dim3 grid((unsigned)(tm * tn));
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  switch (tile) {
+    case 1: hipLaunchKernelGGL((gemm_pair_kernel<128, 128, 32, 32, 16>), grid, dim3(1024), 0, s, g); break;
+    case 2: hipLaunchKernelGGL((gemm_pair_kernel<64, 64, 16, 32, 16>), grid, dim3(512), 0, s, g); break;
+    case 3: hipLaunchKernelGGL((gemm_pair_kernel<32, 64, 16, 16, 32>), grid, dim3(512), 0, s, g); break;
+    default:
+      if (fits) hipLaunchKernelGGL(gemm_f64_kernel<unsigned>, grid, dim3(GT), 0, s, g);
+      else hipLaunchKernelGGL(gemm_f64_kernel<int64_t>, grid, dim3(GT), 0, s, g);
+  }
   return check_hip(hipGetLastError(), "fd_block_gemm_f64 launch");
 }

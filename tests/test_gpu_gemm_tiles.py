@@ -1,0 +1,47 @@
+"""Every tile shape of the block product (fd_block_gemm_f64) at the edges of its tiles and
+K stages, against the FP64 oracle: small integer operands, exact in any order of
+summation, so the products are equal bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as ora
+
+pytestmark = pytest.mark.gpu
+
+api = pytest.importorskip("paper_2506_02486_amd.api")
+
+
+def _check(m, n, k, accumulate, pad=(3, 5, 2)):
+    rng = np.random.default_rng(m + 7 * n + 31 * k)
+    A = rng.integers(-9, 10, (m, k)).astype(np.float64)
+    B = rng.integers(-9, 10, (k, n)).astype(np.float64)
+    C0 = rng.integers(-99, 100, (m, n)).astype(np.float64)
+    dev = []
+    for x, extra in zip((A, B, C0), pad):  # leading dimensions wider than the rows
+        t = torch.full((x.shape[0], x.shape[1] + extra), float("nan"), dtype=torch.float64,
+                       device="cuda")
+        t[:, :x.shape[1]] = torch.from_numpy(x)
+        dev.append(t)
+    a, b, c = dev
+    api.block_gemm(a[:, :k], b[:, :n], c[:, :n], accumulate=accumulate)
+    want = ora.block_gemm(A, B, C0.copy(), accumulate=accumulate)
+    assert np.array_equal(c[:, :n].cpu().numpy(), want)
+    assert bool(torch.isnan(c[:, n:]).all())  # nothing outside C is written
+
+
+# 32 x 64 tiles (stages of 32), 64 x 64 and 128 x 128 (stages of 16)
+@pytest.mark.parametrize("m,n", [(33, 65), (31, 63), (511, 4090), (2045, 2047)])
+@pytest.mark.parametrize("k", [1, 2, 15, 16, 17, 31, 32, 33, 47, 64, 97])
+def test_pair_kernel_tiles(m, n, k):
+    _check(m, n, k, accumulate=k % 2 == 1)
+
+
+@pytest.mark.parametrize("k", [1, 16, 17, 33, 50])
+def test_large_tiles(k):  # 256 x 128
+    _check(4095, 4094, k, accumulate=k % 2 == 1)
+
+
+@pytest.mark.parametrize("ld", [(1 << 23) + 1, (1 << 23) - 1])
+def test_large_leading_dimension(ld):  # 64-bit offsets, and the last 32-bit ones
+    _check(3, 70, 37, True, pad=(ld - 37, 5, 2))
