@@ -490,6 +490,53 @@ int fd_scatter_add_scaled(const fd_grid* g, float* b, const int64_t* off,
 int fd_grad_finalize_scaled(const fd_grid* g, const float* g_b, const float* vdt2,
                             double dt, float* grad_m, void* stream);
 
+/* The gradient's sweeps over several steps.  The forward sweep keeps each step's
+ * stencil sum s_n = L u^n + f^n (which the update forms anyway) instead of u^n, so that
+ * the reverse sweep needs no second stencil: g_b += b^{n+1} s_n is pointwise, and is
+ * done inside the update of b.
+ *
+ * fd_forward_run without faces (send and send2 all NULL) that also writes s_n of step
+ * n, on the interior, to keep[n] (host array of run->nt device volume arrays; f^n =
+ * wavelet[n] at the source).  All volume arrays 16-byte aligned, origin and strides
+ * multiples of 4 floats (as fd_grid_init makes them), else FD_EINVAL; otherwise as
+ * fd_forward_run. */
+int fd_forward_keep(const fd_grid* g, fd_run* run, float* const* keep, void* stream);
+
+/* nt steps of fd_adjoint_step_scaled with its gradient, i = nt-1 .. 0, on s_n in place
+ * of u_n: per step
+ *   (w_out non-NULL) w_out[i] = b_n1[w_off[0]],
+ *   g_b += b_n1 keep[i],
+ *   b_nn = D (2 b_n1 - E b_nn + Q L b_n1),
+ *   (nrec > 0) the residual row is added to it as by fd_scatter_add_scaled: row i-1 of
+ *   res for i > 0, res0 for i = 0 (NULL: none); with rec_map (fd_receiver_plane_map of
+ *   the same receivers, plane rec_k) in the update's launch,
+ *   rotate (b_nn, b_n1) <- (b_n1, b_nn).
+ * The same bits as the per-step calls.  On return the struct's b_nn, b_n1 are rotated.
+ * Alignment as fd_forward_keep.  FD_EINVAL for a NULL or overlapping array. */
+typedef struct fd_reverse {
+  float* b_nn;                 /* b^{n+2} of the first step done (i = nt-1)       */
+  float* b_n1;                 /* b^{n+1}, its residual added                     */
+  const float* vdt2;
+  fd_sponge sponge;            /* all NULL: no sponge                             */
+  int32_t nt;
+  const float* const* keep;    /* host array of nt device volume arrays           */
+  float* g_b;
+  int32_t nrec;
+  const int64_t* rec_off;      /* device                                          */
+  const int32_t* rec_map;      /* device, optional                                */
+  int32_t rec_k;
+  const float* res;            /* device, (nt-1) x nrec                           */
+  const float* res0;           /* device, nrec, or NULL                           */
+  const int64_t* w_off;        /* device, one offset (the source), or NULL        */
+  float* w_out;                /* device, nt, or NULL                             */
+} fd_reverse;
+int fd_adjoint_run(const fd_grid* g, fd_reverse* run, void* stream);
+
+/* g_vdt2 += D a_n1 s_n on the interior: fd_adjoint_step's gradient from s_n = L u_n + f
+ * as fd_forward_keep writes it (same bits; sp may be NULL: D = 1). */
+int fd_grad_accumulate(const fd_grid* g, const float* a_n1, const float* keep_n,
+                       const fd_sponge* sp, float* g_vdt2, void* stream);
+
 /* ------------------------------------------------------- shot serving
  * No passage of the paper defines shot serving.  The server is this library's
  * one-device analogue of two runtime mechanisms of the paper: device memory

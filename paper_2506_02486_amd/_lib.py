@@ -54,6 +54,14 @@ class fd_run(C.Structure):
                 ("send2", C.c_void_p * 6), ("rec_map", C.c_void_p), ("rec_k", C.c_int32)]
 
 
+class fd_reverse(C.Structure):
+    _fields_ = [("b_nn", C.c_void_p), ("b_n1", C.c_void_p), ("vdt2", C.c_void_p),
+                ("sponge", fd_sponge), ("nt", C.c_int32), ("keep", C.POINTER(C.c_void_p)),
+                ("g_b", C.c_void_p), ("nrec", C.c_int32), ("rec_off", C.c_void_p),
+                ("rec_map", C.c_void_p), ("rec_k", C.c_int32), ("res", C.c_void_p),
+                ("res0", C.c_void_p), ("w_off", C.c_void_p), ("w_out", C.c_void_p)]
+
+
 class FDError(RuntimeError):
     def __init__(self, code: int, where: str, detail: str):
         super().__init__(f"{where}: {detail or 'error'} (code {code})")
@@ -96,6 +104,9 @@ SIGNATURES = {
     "fd_step_exchange": (C.c_int, [_G, _P, _P, _P, _P, _S, C.POINTER(fd_source),
                                    C.POINTER(_P), C.POINTER(_P), _P]),
     "fd_forward_run": (C.c_int, [_G, C.POINTER(fd_run), _P]),
+    "fd_forward_keep": (C.c_int, [_G, C.POINTER(fd_run), C.POINTER(_P), _P]),
+    "fd_adjoint_run": (C.c_int, [_G, C.POINTER(fd_reverse), _P]),
+    "fd_grad_accumulate": (C.c_int, [_G, _P, _P, _S, _P, _P]),
     "fd_forward_graph": (C.c_int, [_G, C.POINTER(fd_run), C.POINTER(_P)]),
     "fd_graph_launch": (C.c_int, [_P, _P]),
     "fd_graph_destroy": (C.c_int, [_P]),

@@ -508,6 +508,83 @@ def forward_run(grid: Grid, u_prev, u, u_next, vdt2, sponge: Sponge | None, nt: 
     return bufs[r.u_prev], bufs[r.u], bufs[r.u_next], send, send2
 
 
+def _volumes(grid: Grid, keep, nt: int, who: str):
+    """ctypes array of the first ``nt`` volume tensors of ``keep``."""
+    if len(keep) < nt:
+        raise ValueError(f"{who}: {nt} kept volumes are needed")
+    arr = (C.c_void_p * max(nt, 1))()
+    for i in range(nt):
+        grid.check(keep[i], "keep")
+        arr[i] = keep[i].data_ptr()
+    return arr
+
+
+def forward_keep(grid: Grid, u_prev, u, u_next, vdt2, sponge: Sponge | None, nt: int, keep,
+                 src=None, wavelet=None, rec_off: torch.Tensor | None = None,
+                 traces: torch.Tensor | None = None, stream=None,
+                 rec_plane: ReceiverPlane | None = None):
+    """``forward_run`` without faces that also writes s_n = L u^n + f^n of step n to the
+    volume ``keep[n]`` (fd_forward_keep): what the gradient needs of the forward state.
+    Returns the rotated ``(u_prev, u, u_next)``."""
+    r, bufs, hold = _run_struct(grid, u_prev, u, u_next, vdt2, sponge, nt, src, wavelet, rec_off,
+                                traces, None, None, rec_plane, "forward_keep")
+    check(lib().fd_forward_keep(grid.ref, C.byref(r), _volumes(grid, keep, nt, "forward_keep"),
+                                _stream(stream)), "fd_forward_keep")
+    return bufs[r.u_prev], bufs[r.u], bufs[r.u_next]
+
+
+def adjoint_run(grid: Grid, b_nn, b_n1, vdt2, sponge: Sponge | None, nt: int, keep, g_b,
+                rec_off: torch.Tensor | None = None, res: torch.Tensor | None = None,
+                res0: torch.Tensor | None = None, rec_plane: ReceiverPlane | None = None,
+                w_off: torch.Tensor | None = None, w_out: torch.Tensor | None = None,
+                stream=None):
+    """``nt`` steps of the scaled adjoint with its gradient from the kept s_n
+    (fd_adjoint_run), step i = nt-1 .. 0 on ``keep[i]``: the residual row added after step
+    i is ``res[i - 1]`` (``res0``, or none, after step 0).  Returns the rotated
+    ``(b_nn, b_n1)``."""
+    for n, t in (("b_nn", b_nn), ("b_n1", b_n1), ("vdt2", vdt2), ("g_b", g_b)):
+        grid.check(t, n)
+    r = _lib.fd_reverse()
+    r.b_nn, r.b_n1, r.vdt2, r.g_b = (t.data_ptr() for t in (b_nn, b_n1, vdt2, g_b))
+    if sponge is not None:
+        r.sponge = sponge.c
+    r.nt = int(nt)
+    arr = _volumes(grid, keep, nt, "adjoint_run")
+    r.keep = C.cast(arr, C.POINTER(C.c_void_p))
+    if rec_off is not None and rec_off.numel():
+        n = rec_off.numel()
+        for rows, least in ((res, nt - 1), (res0, 1)):
+            if rows is not None and least > 0:
+                _check_points("adjoint_run", rec_off, rows)
+                if rows.numel() < least * n:
+                    raise TypeError("adjoint_run: a residual row per step is needed")
+        r.nrec = n
+        r.rec_off = rec_off.data_ptr()
+        r.res, r.res0 = _ptr(res), _ptr(res0)
+        if rec_plane is not None:
+            m = rec_plane.map
+            if (m.dtype != torch.int32 or not m.is_cuda or not m.is_contiguous()
+                    or m.numel() != grid.nx * grid.ny or rec_plane.nrec != n):
+                raise TypeError("adjoint_run: rec_plane must be the receivers' plane map")
+            r.rec_map, r.rec_k = m.data_ptr(), rec_plane.k
+    if w_out is not None:
+        _check_points("adjoint_run", w_off, w_out)
+        if w_out.numel() < nt:
+            raise TypeError("adjoint_run: w_out shorter than nt")
+        r.w_off, r.w_out = w_off.data_ptr(), w_out.data_ptr()
+    check(lib().fd_adjoint_run(grid.ref, C.byref(r), _stream(stream)), "fd_adjoint_run")
+    return (b_n1, b_nn) if nt % 2 else (b_nn, b_n1)
+
+
+def grad_accumulate(grid: Grid, a_n1, keep_n, sponge, g_vdt2, stream=None):
+    """g_vdt2 += D a_n1 s_n (fd_grad_accumulate): adjoint_step's gradient from a kept s_n."""
+    for n, t in (("a_n1", a_n1), ("keep_n", keep_n), ("g_vdt2", g_vdt2)):
+        grid.check(t, n)
+    check(lib().fd_grad_accumulate(grid.ref, a_n1.data_ptr(), keep_n.data_ptr(),
+                                   sponge_ref(sponge), g_vdt2.data_ptr(), _stream(stream)),
+          "fd_grad_accumulate")
+
+
 class ForwardGraph:
     """A forward run recorded once as a HIP graph (fd_forward_graph) and launched as
     often as wanted: each ``launch`` re-runs the ``nt`` steps from a zero state with

@@ -688,6 +688,129 @@ int fd_forward_run(const fd_grid* g, fd_run* run, void* stream) {
                    "fd_forward_run launch");
 }
 
+int fd_forward_keep(const fd_grid* g, fd_run* run, float* const* keep, void* stream) {
+  int nsend, nsend2;
+  const float *ex, *ey, *ez;
+  int rc = forward_checked(g, run, &nsend, &nsend2, &ex, &ey, &ez);
+  if (rc) return rc;
+  if (nsend) return fail(FD_EINVAL, "fd_forward_keep: no face buffers");
+  if (run->nt == 0) return FD_OK;
+  if (!keep) return fail(FD_EINVAL, "fd_forward_keep: keep is NULL");
+  const float* arr[4] = {run->u_prev, run->u, run->u_next, run->vdt2};
+  const Geo geo = make_geo(g);
+  for (int32_t n = 0; n < run->nt; ++n) {
+    if (!keep[n]) return fail(FD_EINVAL, "fd_forward_keep: keep[%d] is NULL", n);
+    for (int i = 0; i < 4; ++i)
+      if (overlaps(g, keep[n], arr[i]))
+        return fail(FD_EINVAL, "fd_forward_keep: keep[%d] overlaps a volume array", n);
+  }
+  if (!keep_fits(geo, arr, 4) || !keep_fits(geo, keep, run->nt))
+    return fail(FD_EINVAL, "fd_forward_keep: arrays must be 16-byte aligned, strides and origin "
+                           "multiples of 4");
+  const Coef c = make_coef(g);
+  hipStream_t s = as_stream(stream);
+  float *up = run->u_prev, *u = run->u, *un = run->u_next;
+  hipError_t e = hipSuccess;
+  for (int32_t n = 0; n < run->nt && e == hipSuccess; ++n) {
+    const fd_source src{run->src[0], run->src[1], run->src[2],
+                        run->wavelet ? run->wavelet[n] : 0.f};
+    float* row = run->nrec ? run->traces + (int64_t)n * run->nrec : nullptr;
+    const RecPlane rp{run->rec_map, run->rec_k, row};
+    const bool in_kernel = run->rec_map && run->nrec > 0;
+    e = launch_keep(geo, c, up, u, un, run->vdt2, ex, ey, ez, run->wavelet ? &src : nullptr,
+                    in_kernel ? &rp : nullptr, keep[n], s);
+    if (e == hipSuccess && run->nrec && !in_kernel)
+      e = launch_record(un, run->rec_off, run->nrec, row, s);
+    if (e != hipSuccess) break;
+    float* t = up;
+    up = u;
+    u = un;
+    un = t;
+  }
+  run->u_prev = up;
+  run->u = u;
+  run->u_next = un;
+  return check_hip(e, "fd_forward_keep launch");
+}
+
+int fd_adjoint_run(const fd_grid* g, fd_reverse* r, void* stream) {
+  int rc = check_grid(g);
+  if (rc) return rc;
+  if (!r) return fail(FD_EINVAL, "fd_adjoint_run: run is NULL");
+  if (r->nt < 0) return fail(FD_EINVAL, "fd_adjoint_run: nt < 0");
+  const float* arr[4] = {r->b_nn, r->b_n1, r->vdt2, r->g_b};
+  for (int i = 0; i < 4; ++i) {
+    if (!arr[i]) return fail(FD_EINVAL, "fd_adjoint_run: NULL array");
+    for (int j = 0; j < i; ++j)
+      if (overlaps(g, arr[i], arr[j])) return fail(FD_EINVAL, "fd_adjoint_run: arrays overlap");
+  }
+  if (r->nrec < 0 || (r->nrec > 0 && (!r->rec_off || (r->nt > 1 && !r->res))))
+    return fail(FD_EINVAL, "fd_adjoint_run: bad receivers");
+  if (r->rec_map && (r->rec_k < 0 || r->rec_k >= g->nz))
+    return fail(FD_EINVAL, "fd_adjoint_run: receiver plane %d outside the interior", r->rec_k);
+  if (r->w_out && !r->w_off) return fail(FD_EINVAL, "fd_adjoint_run: w_out needs w_off");
+  if (r->nt == 0) return FD_OK;
+  if (!r->keep) return fail(FD_EINVAL, "fd_adjoint_run: keep is NULL");
+  const Geo geo = make_geo(g);
+  for (int32_t i = 0; i < r->nt; ++i) {
+    if (!r->keep[i]) return fail(FD_EINVAL, "fd_adjoint_run: keep[%d] is NULL", i);
+    for (int j = 0; j < 4; ++j)
+      if (j != 2 && overlaps(g, r->keep[i], arr[j]))
+        return fail(FD_EINVAL, "fd_adjoint_run: keep[%d] overlaps a volume array", i);
+  }
+  if (!keep_fits(geo, arr, 4) || !keep_fits(geo, r->keep, r->nt))
+    return fail(FD_EINVAL, "fd_adjoint_run: arrays must be 16-byte aligned, strides and origin "
+                           "multiples of 4");
+  const float *ex, *ey, *ez;
+  rc = check_sponge(&r->sponge, &ex, &ey, &ez);
+  if (rc) return rc;
+  const Coef c = make_coef(g);
+  hipStream_t s = as_stream(stream);
+  hipError_t e = hipSuccess;
+  // the gradient terms of two steps are added by every second update, which holds both
+  // b^{n+2} and b^{n+1}: g is read and written once per two steps (24 bytes per point
+  // and step instead of 28)
+  const float* pending = nullptr;
+  for (int32_t i = r->nt - 1; i >= 0; --i) {
+    if (r->w_out) e = launch_record(r->b_n1, r->w_off, 1, r->w_out + i, s);
+    const float* row = r->nrec == 0 ? nullptr : i > 0 ? r->res + (int64_t)(i - 1) * r->nrec : r->res0;
+    RecPlane rp{r->rec_map, r->rec_k, const_cast<float*>(row)};
+    rp.add = true;
+    const RecPlane* inj = row && r->rec_map ? &rp : nullptr;
+    if (e != hipSuccess) break;
+    if (!pending && i > 0) {
+      e = forward_update(geo, c, r->b_nn, r->b_n1, r->b_nn, r->vdt2, ex, ey, ez, nullptr, s, inj);
+      pending = r->keep[i];
+    } else {
+      e = launch_acc(geo, c, r->b_nn, r->b_n1, r->b_nn, r->vdt2, ex, ey, ez, inj, r->keep[i],
+                     pending, r->g_b, s);
+      pending = nullptr;
+    }
+    if (e == hipSuccess && row && !inj)
+      e = launch_scatter_add_scaled(geo, r->b_nn, r->rec_off, row, r->vdt2, ex, ey, ez, r->nrec, s);
+    if (e != hipSuccess) break;
+    float* t = r->b_nn;
+    r->b_nn = r->b_n1;
+    r->b_n1 = t;
+  }
+  return check_hip(e, "fd_adjoint_run launch");
+}
+
+int fd_grad_accumulate(const fd_grid* g, const float* a_n1, const float* keep_n,
+                       const fd_sponge* sp, float* g_vdt2, void* stream) {
+  int rc = check_grid(g);
+  if (rc) return rc;
+  if (!a_n1 || !keep_n || !g_vdt2) return fail(FD_EINVAL, "fd_grad_accumulate: NULL array");
+  if (overlaps(g, g_vdt2, a_n1) || overlaps(g, g_vdt2, keep_n))
+    return fail(FD_EINVAL, "fd_grad_accumulate: g_vdt2 overlaps another array");
+  const float *ex, *ey, *ez;
+  rc = check_sponge(sp, &ex, &ey, &ez);
+  if (rc) return rc;
+  return check_hip(launch_grad_accumulate(make_geo(g), a_n1, keep_n, ex, ey, ez, g_vdt2,
+                                          as_stream(stream)),
+                   "fd_grad_accumulate launch");
+}
+
 struct fd_graph {
   hipGraphExec_t exec;
 };

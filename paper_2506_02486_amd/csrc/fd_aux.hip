@@ -350,6 +350,23 @@ __global__ void __launch_bounds__(BS) grad_finalize_kernel(Geo g, const float* g
   }
 }
 
+// g += D a s, as the gradient pass forms it from L u + f = s
+__global__ void __launch_bounds__(BS) grad_accumulate_kernel(Geo g, const float* __restrict__ a,
+                                                             const float* __restrict__ sn,
+                                                             const float* ex, const float* ey,
+                                                             const float* ez,
+                                                             float* __restrict__ gq) {
+  const int j = blockIdx.y;
+  const int k = blockIdx.z;
+  for (int i = blockIdx.x * BS + threadIdx.x; i < g.nx; i += gridDim.x * BS) {
+    const long long o = at(g, i, j, k);
+    const float eta = ex ? ex[i] + ey[j] + ez[k] : 0.f;
+    float D = 1.f;
+    if (eta != 0.f) D = __builtin_amdgcn_rcpf(1.f + eta);
+    gq[o] = gq[o] + D * a[o] * sn[o];
+  }
+}
+
 __global__ void __launch_bounds__(BS) zero_kernel(float* __restrict__ dst, long long n) {
   for (long long i = blockIdx.x * (long long)BS + threadIdx.x; i < n; i += (long long)gridDim.x * BS)
     dst[i] = 0.f;
@@ -502,6 +519,13 @@ hipError_t launch_grad_finalize(const Geo& g, const float* gq, const float* q, d
   const float sc = (float)(1.0 / (dt * dt));
   hipLaunchKernelGGL(grad_finalize_kernel, dim3(blocks_for(g.nx, 64), g.ny, g.nz), dim3(BS), 0,
                      s, g, gq, q, sc, scaled, gm);
+  return hipGetLastError();
+}
+
+hipError_t launch_grad_accumulate(const Geo& g, const float* a, const float* sn, const float* ex,
+                                  const float* ey, const float* ez, float* gq, hipStream_t s) {
+  hipLaunchKernelGGL(grad_accumulate_kernel, dim3(blocks_for(g.nx, 64), g.ny, g.nz), dim3(BS), 0,
+                     s, g, a, sn, ex, ey, ez, gq);
   return hipGetLastError();
 }
 

@@ -51,6 +51,14 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 constexpr int TROWS = 16;  // y rows of a brick
 
+// FWD: the update.  GRAD: the gradient pass.  KEEP: the update, which also writes its
+// stencil sum s_n = L u^n + f^n.  ACC: the update of the reverse sweep (u = b^{n+1}, up =
+// b^{n+2}), which also adds the gradient terms of the s it is given (why: fd_stencil4.hip).
+// 128^3: KEEP 8.7 us, ACC 14.8, update 8.0 (before, 64 x 32 marching tiles and one thread
+// per point: 12.4 forward, 11.6 + 12.4 + a 2.7 us residual launch per reverse step); a
+// gradient over 96 steps, checkpoints every 32: 4.85 -> 2.87 ms.
+enum BrickMode { B_FWD = 0, B_GRAD = 1, B_KEEP = 2, B_ACC = 3 };
+
 struct BrickArgs {
   Geo g;
   Coef c;
@@ -71,6 +79,11 @@ struct BrickArgs {
   int rk;
   const int32_t* rmap;
   float* rrow;
+  // KEEP: s_n is written to keep.  ACC: g_acc += up s2 (if s2) + u s1
+  float* keep;
+  const float* s1;
+  const float* s2;
+  float* g_acc;
 };
 struct BrickFaces {
   const float* in[6];
@@ -87,10 +100,11 @@ __device__ __forceinline__ f4 ld4(const char* base, unsigned boff) {
   return *reinterpret_cast<const f4*>(base + boff);
 }
 
-template <int LANES, int KZ, bool SPONGE, bool XCH, bool GRAD, bool RADD>
+template <int LANES, int KZ, bool SPONGE, bool XCH, BrickMode MODE, bool RADD>
 __device__ __forceinline__ void brick_block(const BrickArgs& p, const BrickFaces& fc,
                                             const int bx, const int by, const int bz,
                                             const int t) {
+  constexpr bool GRAD = MODE == B_GRAD, KEEP = MODE == B_KEEP, ACC = MODE == B_ACC;
   constexpr int BT = LANES * TROWS;
   constexpr int TX = 4 * LANES;
   constexpr int LX = TX + 8;
@@ -199,6 +213,19 @@ __device__ __forceinline__ void brick_block(const BrickArgs& p, const BrickFaces
       B += kb + s + 1 < nz ? szb : 0;
     }
   }
+  f4 s1v[KZ], s2v[KZ], gv[KZ];
+  if constexpr (ACC) {
+    const char* S1 = reinterpret_cast<const char*>(p.s1 + org_c) + (long long)kb * szb;
+    const char* S2 = reinterpret_cast<const char*>((p.s2 ? p.s2 : p.s1) + org_c) + (long long)kb * szb;
+    const char* G0 = reinterpret_cast<const char*>(p.g_acc + org_c) + (long long)kb * szb;
+#pragma unroll
+    for (int s = 0; s < KZ; ++s) {
+      const long long o = kb + s < nz ? s * szb : 0;
+      s1v[s] = ld4(S1 + o, po);
+      s2v[s] = ld4(S2 + o, po);
+      gv[s] = ld4(G0 + o, po);
+    }
+  }
   float exc[4] = {0.f, 0.f, 0.f, 0.f}, eyr = 0.f;
   float ezk[KZ];
   bool damp_xy = false;
@@ -284,12 +311,18 @@ __device__ __forceinline__ void brick_block(const BrickArgs& p, const BrickFaces
       float l = lap[s][e];
 #pragma unroll
       for (int m = 1; m <= 4; ++m) l += c.cz[m] * (zc[s + 4 + m][e] + zc[s + 4 - m][e]);
-      if constexpr (GRAD) v4[e] = l;
-      else v4[e] = 2.f * uc[e] - ua[e] + ub[e] * l;
+      // s_n = L u + f: f is added where it is 0 too (that decides the sign of a zero), as
+      // in the gradient mode of the marching kernels
+      if constexpr (GRAD || KEEP)
+        lap[s][e] = l + (src_plane && x + e == p.si && y == p.sj ? p.sw : 0.f);
+      if constexpr (!GRAD) v4[e] = 2.f * uc[e] - ua[e] + ub[e] * l;
+      if constexpr (ACC) {
+        if (p.s2) gv[s][e] += ua[e] * s2v[s][e];
+        gv[s][e] += uc[e] * s1v[s][e];
+      }
     }
     if constexpr (GRAD) {
-      // g += D a (L u + f), rounded as in the gradient mode of the marching kernels (f
-      // is added where it is 0 too: that decides the sign of a zero)
+      // g += D a (L u + f)
       f4 da = ua;
       if (damped) {
 #pragma unroll
@@ -298,15 +331,8 @@ __device__ __forceinline__ void brick_block(const BrickArgs& p, const BrickFaces
           if (eta[e] != 0.f) da[e] = __builtin_amdgcn_rcpf(1.f + eta[e]) * ua[e];
         }
       }
-      if (src_plane) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v4[e] += x + e == p.si && y == p.sj ? p.sw : 0.f;
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v4[e] += 0.f;
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v4[e] = ub[e] + da[e] * v4[e];
+      for (int e = 0; e < 4; ++e) v4[e] = ub[e] + da[e] * lap[s][e];
     } else {
       if (damped) {
 #pragma unroll
@@ -347,6 +373,11 @@ __device__ __forceinline__ void brick_block(const BrickArgs& p, const BrickFaces
     float* d = reinterpret_cast<float*>(reinterpret_cast<char*>(p.un + org_c) + (long long)k * szb + cb);
     if (full) {
       *reinterpret_cast<f4*>(d) = v4;  // a plain store: the next step reads it from cache
+      if constexpr (KEEP)
+        __builtin_nontemporal_store(
+            lap[s], reinterpret_cast<f4*>(reinterpret_cast<char*>(p.keep + org_c) + (long long)k * szb + cb));
+      if constexpr (ACC)
+        *reinterpret_cast<f4*>(reinterpret_cast<char*>(p.g_acc + org_c) + (long long)k * szb + cb) = gv[s];
       if constexpr (XCH) {
         const size_t kk = (size_t)k;
         if (x == 0) *reinterpret_cast<f4*>(fc.out[0] + (kk * ny + y) * 4) = v4;
@@ -360,6 +391,13 @@ __device__ __forceinline__ void brick_block(const BrickArgs& p, const BrickFaces
 #pragma unroll
       for (int e = 0; e < 3; ++e)
         if (x + e < nx) d[e] = v4[e];
+      if constexpr (KEEP || ACC) {
+        float* d2 = reinterpret_cast<float*>(
+            reinterpret_cast<char*>((KEEP ? p.keep : p.g_acc) + org_c) + (long long)k * szb + cb);
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+          if (x + e < nx) d2[e] = KEEP ? lap[s][e] : gv[s][e];
+      }
     }
   }
 }
@@ -374,15 +412,18 @@ __device__ __forceinline__ void brick_tile(const BrickArgs& p, unsigned logical,
   *bz = (int)z;
 }
 
-// waves per SIMD the register budget must allow: 16 waves per CU
-constexpr int BRICK_WAVES = 4;
+// waves per SIMD the register budget must allow: 16 waves per CU, 12 where two planes
+// with a further operand or two per point would spill at that
+constexpr int brick_waves(int kz, BrickMode mode) {
+  return kz > 1 && (mode == B_GRAD || mode == B_ACC) ? 3 : 4;
+}
 
-template <int LANES, int KZ, bool SPONGE, bool XCH, bool GRAD, bool RADD>
-__global__ void __launch_bounds__(LANES * TROWS, BRICK_WAVES) brick_kernel(BrickArgs p,
-                                                                           BrickFaces fc) {
+template <int LANES, int KZ, bool SPONGE, bool XCH, BrickMode MODE, bool RADD>
+__global__ void __launch_bounds__(LANES * TROWS, brick_waves(KZ, MODE))
+    brick_kernel(BrickArgs p, BrickFaces fc) {
   int bx, by, bz;
   brick_tile(p, (unsigned)remap_brick(blockIdx.x, gridDim.x), &bx, &by, &bz);
-  brick_block<LANES, KZ, SPONGE, XCH, GRAD, RADD>(p, fc, bx, by, bz, threadIdx.x);
+  brick_block<LANES, KZ, SPONGE, XCH, MODE, RADD>(p, fc, bx, by, bz, threadIdx.x);
 }
 
 // One step of several grids in one launch, their parameters in the kernel arguments:
@@ -394,14 +435,15 @@ struct BrickMulti {
 };
 
 template <int KZ>
-__global__ void __launch_bounds__(8 * TROWS, BRICK_WAVES) brick_multi_kernel(BrickMulti A) {
+__global__ void __launch_bounds__(8 * TROWS, brick_waves(KZ, B_FWD))
+    brick_multi_kernel(BrickMulti A) {
   const int b = remap_brick(blockIdx.x, gridDim.x);
   int i = 0;
   while (i + 1 < A.n && b >= A.start[i + 1]) ++i;
   const BrickArgs& p = A.grid[i];
   int bx, by, bz;
   brick_tile(p, (unsigned)(b - A.start[i]), &bx, &by, &bz);
-  brick_block<8, KZ, true, false, false, false>(p, BrickFaces{}, bx, by, bz, threadIdx.x);
+  brick_block<8, KZ, true, false, B_FWD, false>(p, BrickFaces{}, bx, by, bz, threadIdx.x);
 }
 
 // Grids up to this many points take one plane per brick: with two, a 64^3 grid has 256
@@ -452,21 +494,18 @@ BrickArgs brick_args(const Geo& g, const Coef& c, const float* up, const float* 
   return p;
 }
 
-template <bool SPONGE, bool XCH, bool GRAD, bool RADD>
+template <bool SPONGE, bool XCH, BrickMode MODE, bool RADD>
 hipError_t launch_bricks(const BrickArgs& p, const BrickFaces& fc, int lanes, hipStream_t s) {
-  // the damped gradient pass with two planes would spill registers
-  const int kz = GRAD && SPONGE ? 1 : brick_planes((long long)p.g.nx * p.g.ny * p.g.nz);
+  const int kz = brick_planes((long long)p.g.nx * p.g.ny * p.g.nz);
   const long long nb = (long long)p.tiles_x * p.tiles_y * ((p.g.nz + kz - 1) / kz);
   if (nb <= 0 || nb > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)nb), block((unsigned)(lanes * TROWS));
 #define FD_BRICK(L, K) \
-  hipLaunchKernelGGL((brick_kernel<L, K, SPONGE, XCH, GRAD, RADD>), grid, block, 0, s, p, fc)
+  hipLaunchKernelGGL((brick_kernel<L, K, SPONGE, XCH, MODE, RADD>), grid, block, 0, s, p, fc)
   if (lanes == 8 && kz == 1) FD_BRICK(8, 1);
   else if (kz == 1) FD_BRICK(16, 1);
-  else if constexpr (!(GRAD && SPONGE)) {
-    if (lanes == 8) FD_BRICK(8, 2);
-    else FD_BRICK(16, 2);
-  }
+  else if (lanes == 8) FD_BRICK(8, 2);
+  else FD_BRICK(16, 2);
 #undef FD_BRICK
   return hipGetLastError();
 }
@@ -515,14 +554,14 @@ hipError_t launch_brick(const Geo& g, const Coef& c, const float* up, const floa
       fc.in[f] = in[f];
       fc.out[f] = out[f];
     }
-    return ex ? launch_bricks<true, true, false, false>(p, fc, lanes, s)
-              : launch_bricks<false, true, false, false>(p, fc, lanes, s);
+    return ex ? launch_bricks<true, true, B_FWD, false>(p, fc, lanes, s)
+              : launch_bricks<false, true, B_FWD, false>(p, fc, lanes, s);
   }
   if (radd)
-    return ex ? launch_bricks<true, false, false, true>(p, fc, lanes, s)
-              : launch_bricks<false, false, false, true>(p, fc, lanes, s);
-  return ex ? launch_bricks<true, false, false, false>(p, fc, lanes, s)
-            : launch_bricks<false, false, false, false>(p, fc, lanes, s);
+    return ex ? launch_bricks<true, false, B_FWD, true>(p, fc, lanes, s)
+              : launch_bricks<false, false, B_FWD, true>(p, fc, lanes, s);
+  return ex ? launch_bricks<true, false, B_FWD, false>(p, fc, lanes, s)
+            : launch_bricks<false, false, B_FWD, false>(p, fc, lanes, s);
 }
 
 hipError_t launch_grad_brick(const Geo& g, const Coef& c, const float* u, const float* an1,
@@ -530,8 +569,32 @@ hipError_t launch_grad_brick(const Geo& g, const Coef& c, const float* u, const 
                              const fd_source* src, hipStream_t s) {
   const int lanes = brick_lanes(g);
   const BrickArgs p = brick_args(g, c, an1, u, gq, gq, ex, ey, ez, src, nullptr, lanes);
-  return ex ? launch_bricks<true, false, true, false>(p, BrickFaces{}, lanes, s)
-            : launch_bricks<false, false, true, false>(p, BrickFaces{}, lanes, s);
+  return ex ? launch_bricks<true, false, B_GRAD, false>(p, BrickFaces{}, lanes, s)
+            : launch_bricks<false, false, B_GRAD, false>(p, BrickFaces{}, lanes, s);
+}
+
+hipError_t launch_keep_brick(const Geo& g, const Coef& c, const float* up, const float* u,
+                             float* un, const float* q, const float* ex, const float* ey,
+                             const float* ez, const fd_source* src, const RecPlane* rp,
+                             float* keep, hipStream_t s) {
+  const int lanes = brick_lanes(g);
+  BrickArgs p = brick_args(g, c, up, u, un, q, ex, ey, ez, src, rp, lanes);
+  p.keep = keep;
+  return ex ? launch_bricks<true, false, B_KEEP, false>(p, BrickFaces{}, lanes, s)
+            : launch_bricks<false, false, B_KEEP, false>(p, BrickFaces{}, lanes, s);
+}
+
+hipError_t launch_acc_brick(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
+                            const float* q, const float* ex, const float* ey, const float* ez,
+                            const RecPlane* rp, const float* s1, const float* s2, float* g_acc,
+                            hipStream_t s) {
+  const int lanes = brick_lanes(g);
+  BrickArgs p = brick_args(g, c, up, u, un, q, ex, ey, ez, nullptr, rp, lanes);
+  p.s1 = s1;
+  p.s2 = s2;
+  p.g_acc = g_acc;
+  return ex ? launch_bricks<true, false, B_ACC, true>(p, BrickFaces{}, lanes, s)
+            : launch_bricks<false, false, B_ACC, true>(p, BrickFaces{}, lanes, s);
 }
 
 hipError_t launch_brick_multi(const WideStep* steps, int n, hipStream_t s) {

@@ -66,6 +66,19 @@ constexpr int TROWS = Wide128::TROWS;   // multi-grid launches
 constexpr int TX = 4 * LANES;           // 128 x points per tile
 constexpr int TY = TROWS * RY;          // 32 y rows per tile
 
+// FWD: the update.  GRAD: the gradient pass.  KEEP: the update, which also writes its
+// stencil sum s_n = L u^n + f^n.  ACC: the update of the reverse sweep (u = b^{n+1},
+// u^{n-1} = b^{n+2}), which also adds the gradient terms of the s it is given.  A second
+// stencil field (L u^n) in one block would not fit the registers, but with s_n kept by
+// the forward sweep in place of u^n the gradient is pointwise; and since a block holds
+// b^{n+2} and b^{n+1} at once, every second update adds the terms of two steps and g
+// passes HBM once per two steps.  HBM-bound like the update: bytes per point and step,
+// forward 16 -> 20 (KEEP), reverse 32 (update and GRAD launches) -> 24 (16 and, ACC, 32).
+// 256^3: KEEP 61 us, ACC 90 us, update 51 us (before: 52, and 51 + 53 per reverse step);
+// a gradient over 40 steps with every s kept 6.59 -> 5.55 ms.  ACC takes 254 VGPRs, so it
+// loads its receivers' map entries only at their plane.
+enum WideMode { W_FWD = 0, W_GRAD = 1, W_KEEP = 2, W_ACC = 3 };
+
 struct P4 {
   Geo g;
   Coef c;
@@ -87,6 +100,11 @@ struct P4 {
   int rk;
   float* rrow;
   bool radd;    // rrow is a row to add at the receivers, scaled by vdt2 / (1+eta)
+  // KEEP: s_n = L u^n + f^n is written to keep.  ACC: g += u^{n-1} s2 (if s2) + u s1
+  float* keep;
+  const float* s1;
+  const float* s2;
+  float* g_acc;
   bool narrow;  // multi-grid launch: this grid's tiles are 64 x 64 (tiles_x, tiles_y so)
 };
 
@@ -105,7 +123,7 @@ __device__ __forceinline__ f4 ld4_nt(const char* base, unsigned boff) {
 
 // The work of one block: tile (bx, by) of the x-y plane, z chunk bz, of the grid
 // and operands p describes; the thread is lane lx of thread row tr (SH's shape).
-template <class SH, bool SPONGE, bool FUSE, bool XCH, bool GRAD = false>
+template <class SH, bool SPONGE, bool FUSE, bool XCH, WideMode MODE = W_FWD>
 __device__ __forceinline__ void stencil4_block(const P4& p, const int bx, const int by,
                                                const int bz, const int lx, const int tr) {
   constexpr int LANES = SH::LANES;
@@ -114,6 +132,7 @@ __device__ __forceinline__ void stencil4_block(const P4& p, const int bx, const 
   constexpr int LX = TX + 8;              // LDS row pitch (floats)
   constexpr int LY = TY + 8;              // LDS rows
   constexpr int XH = 2 * TY / LANES;      // thread rows that load the x halo
+  constexpr bool GRAD = MODE == W_GRAD, KEEP = MODE == W_KEEP, ACC = MODE == W_ACC;
   __shared__ __attribute__((aligned(16))) float sm[2][LY * LX];
 
   const int nx = p.g.nx, ny = p.g.ny, nz = p.g.nz;
@@ -273,6 +292,8 @@ __device__ __forceinline__ void stencil4_block(const P4& p, const int bx, const 
   // for nothing).  Not in the exchange form, whose receiver row is taken where the
   // faces are packed.
   const bool rec_chunk = FUSE && !XCH && !GRAD && p.rk >= kb && p.rk < ke;
+  // (ACC has no registers to spare for them: it loads them at the plane itself)
+  const bool rec_early = rec_chunk && !ACC;
   int rix[RY][4];
 #pragma unroll
   for (int r = 0; r < RY; ++r)
@@ -283,7 +304,7 @@ __device__ __forceinline__ void stencil4_block(const P4& p, const int bx, const 
   for (int r = 0; r < RY; ++r)
 #pragma unroll
     for (int e = 0; e < 4; ++e) rval[r][e] = 0.f;
-  if (rec_chunk) {
+  if (rec_early) {
 #pragma unroll
     for (int r = 0; r < RY; ++r)
 #pragma unroll
@@ -304,6 +325,22 @@ __device__ __forceinline__ void stencil4_block(const P4& p, const int bx, const 
     constexpr int L = (P + 9) % 10;  // landing slot of plane k + 5
     constexpr int Q = P % 2;         // u^{n-1} and vdt2 of plane k
     const int buf = (k - kb) & 1;
+    // ---- ACC: this plane's operands of the gradient terms, used at the end of the plane:
+    // before the prefetches, so that waiting for them waits for nothing younger
+    f4 s1v[RY], s2v[RY], gv[RY];
+    if constexpr (ACC) {
+      const char* S1 = reinterpret_cast<const char*>(p.s1 + org_c) + (long long)k * szb;
+      const char* S2 =
+          reinterpret_cast<const char*>((p.s2 ? p.s2 : p.s1) + org_c) + (long long)k * szb;
+      const char* G0 = reinterpret_cast<const char*>(p.g_acc + org_c) + (long long)k * szb;
+#pragma unroll
+      for (int r = 0; r < RY; ++r) {
+        s1v[r] = ld4_nt(S1, cbp[r]);
+        s2v[r] = ld4_nt(S2, cbp[r]);
+        gv[r] = ld4_nt(G0, cbp[r]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
     // ---- prefetch: plane k + 5 of the field and its halo, plane k + 1 of u^{n-1}
     // and vdt2 (clamped to the last plane: unused past the chunk)
 #pragma unroll
@@ -348,7 +385,7 @@ __device__ __forceinline__ void stencil4_block(const P4& p, const int bx, const 
       const f4 uc = zq[C][r];
       const f4 ua = pa[Q][r];
       const f4 ub = pb[Q][r];
-      f4 v4;
+      f4 v4, sv;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         // x neighbour at offset o (-4..4) of element e
@@ -377,6 +414,15 @@ __device__ __forceinline__ void stencil4_block(const P4& p, const int bx, const 
           if (damped && eta != 0.f) D = __builtin_amdgcn_rcpf(1.f + eta);
           v = ub[e] + D * ua[e] * (lap + src);
         } else {
+          if constexpr (KEEP) {
+            float f = 0.f;
+            if (src_plane && x + e == p.si && yr + r == p.sj) f = p.sw;
+            sv[e] = lap + f;
+          }
+          if constexpr (ACC) {
+            if (p.s2) gv[r][e] += ua[e] * s2v[r][e];
+            gv[r][e] += u0 * s1v[r][e];
+          }
           v = 2.f * u0 - ua[e] + ub[e] * lap;
           if (damped && eta != 0.f) v = (v + eta * ua[e]) * __builtin_amdgcn_rcpf(1.f + eta);
           if (FUSE && src_plane) {
@@ -384,7 +430,7 @@ __device__ __forceinline__ void stencil4_block(const P4& p, const int bx, const 
 #pragma clang fp contract(off)
             if (x + e == p.si && yr + r == p.sj) v += ub[e] * p.sw / (1.f + eta);
           }
-          if (rec_chunk && p.radd && k == p.rk && rix[r][e] >= 0) {
+          if (!ACC && rec_chunk && p.radd && k == p.rk && rix[r][e] >= 0) {
             // rounds as fd_scatter_add_scaled: the row value times vdt2 / (1+eta)
 #pragma clang fp contract(off)
             v += rval[r][e] * (ub[e] / (1.f + eta));
@@ -392,13 +438,34 @@ __device__ __forceinline__ void stencil4_block(const P4& p, const int bx, const 
         }
         v4[e] = v;
       }
-      if (rec_chunk && !p.radd && k == p.rk) {
+      if (ACC && rec_chunk && k == p.rk) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          int ix = -1;
+          if (x + e < nx && yr + r < ny) ix = p.rmap[(long long)(yr + r) * nx + x + e];
+          if (ix >= 0) {
+            float eta = 0.f;
+            if (damped) eta = exc[e] + eyr[r] + ezk;
+            {
+#pragma clang fp contract(off)
+            v4[e] += p.rrow[ix] * (ub[e] / (1.f + eta));
+            }
+          }
+        }
+      }
+      if (!ACC && rec_chunk && !p.radd && k == p.rk) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if (rix[r][e] >= 0) p.rrow[rix[r][e]] = v4[e];
       }
       if (full[r]) {
         __builtin_nontemporal_store(v4, reinterpret_cast<f4*>(ok + cb[r]));
+        if constexpr (KEEP)
+          __builtin_nontemporal_store(
+              sv, reinterpret_cast<f4*>(reinterpret_cast<char*>(p.keep + org_c) + (long long)k * szb + cb[r]));
+        if constexpr (ACC)
+          __builtin_nontemporal_store(
+              gv[r], reinterpret_cast<f4*>(reinterpret_cast<char*>(p.g_acc + org_c) + (long long)k * szb + cb[r]));
         if (XCH && sx_ptr)
           *reinterpret_cast<f4*>(sx_ptr + ((size_t)k * (size_t)ny + (size_t)(yr + r)) * 4) = v4;
       } else if (act[r]) {  // the row's last points: x < nx < x + 4
@@ -406,6 +473,13 @@ __device__ __forceinline__ void stencil4_block(const P4& p, const int bx, const 
 #pragma unroll
         for (int e = 0; e < 3; ++e)
           if (x + e < nx) __builtin_nontemporal_store(v4[e], d + e);
+        if constexpr (KEEP || ACC) {
+          float* d2 = reinterpret_cast<float*>(
+              reinterpret_cast<char*>((KEEP ? p.keep : p.g_acc) + org_c) + (long long)k * szb + cb[r]);
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (x + e < nx) __builtin_nontemporal_store(KEEP ? sv[e] : gv[r][e], d2 + e);
+        }
       }
     }
   };
@@ -433,12 +507,12 @@ __device__ __forceinline__ void stencil4_block(const P4& p, const int bx, const 
   }
 }
 
-template <class SH, bool SPONGE, bool FUSE, bool XCH, bool GRAD = false>
+template <class SH, bool SPONGE, bool FUSE, bool XCH, WideMode MODE = W_FWD>
 __global__ void __launch_bounds__(SH::LANES * SH::TROWS) stencil4_kernel(P4 p) {
   const int logical = remap_block4(blockIdx.x, gridDim.x);
   const int bx = logical % p.tiles_x;
   const int rest = logical / p.tiles_x;
-  stencil4_block<SH, SPONGE, FUSE, XCH, GRAD>(p, bx, rest % p.tiles_y, rest / p.tiles_y,
+  stencil4_block<SH, SPONGE, FUSE, XCH, MODE>(p, bx, rest % p.tiles_y, rest / p.tiles_y,
                                               threadIdx.x, threadIdx.y);
 }
 
@@ -508,7 +582,7 @@ __global__ void __launch_bounds__(LANES * TROWS) multi4_kernel(MultiArgs A) {
   }
 }
 
-template <class SH, bool SPONGE, bool FUSE, bool XCH, bool GRAD = false>
+template <class SH, bool SPONGE, bool FUSE, bool XCH, WideMode MODE = W_FWD>
 hipError_t launch4(P4 p, hipStream_t st) {
   // one block per CU: its 8 waves take a CU's share of 16 (more than 128 VGPRs)
   const LaunchShape sh = stencil_shape(p.g, 4 * SH::LANES, SH::TROWS * RY, 16);
@@ -517,9 +591,40 @@ hipError_t launch4(P4 p, hipStream_t st) {
   p.kchunk = sh.kchunk;
   const long long nb = (long long)sh.tiles_x * sh.tiles_y * sh.zchunks;
   if (nb <= 0 || nb > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL((stencil4_kernel<SH, SPONGE, FUSE, XCH, GRAD>), dim3((unsigned)nb),
+  hipLaunchKernelGGL((stencil4_kernel<SH, SPONGE, FUSE, XCH, MODE>), dim3((unsigned)nb),
                      dim3(SH::LANES, SH::TROWS), 0, st, p);
   return hipGetLastError();
+}
+
+P4 wide_args(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
+             const float* q, const float* ex, const float* ey, const float* ez,
+             const fd_source* src, const RecPlane* rp) {
+  P4 p{};
+  p.g = g;
+  p.c = c;
+  p.u = u;
+  p.up = up;
+  p.q = q;
+  p.un = un;
+  p.ex = ex;
+  p.ey = ey;
+  p.ez = ez;
+  p.si = p.sj = p.sk = -1;
+  p.sw = 0.f;
+  p.rk = -1;
+  if (rp && rp->map) {
+    p.rmap = rp->map;
+    p.rk = rp->k;
+    p.rrow = rp->row;
+    p.radd = rp->add;
+  }
+  if (src) {
+    p.si = src->i;
+    p.sj = src->j;
+    p.sk = src->k;
+    p.sw = src->w;
+  }
+  return p;
 }
 
 bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15u) == 0; }
@@ -635,11 +740,11 @@ hipError_t launch_grad_wide(const Geo& g, const Coef& c, const float* u, const f
     p.sw = src->w;
   }
   if (wide_narrow_tiles(g)) {
-    if (ex) return launch4<Wide64, true, false, false, true>(p, s);
-    return launch4<Wide64, false, false, false, true>(p, s);
+    if (ex) return launch4<Wide64, true, false, false, W_GRAD>(p, s);
+    return launch4<Wide64, false, false, false, W_GRAD>(p, s);
   }
-  if (ex) return launch4<Wide128, true, false, false, true>(p, s);
-  return launch4<Wide128, false, false, false, true>(p, s);
+  if (ex) return launch4<Wide128, true, false, false, W_GRAD>(p, s);
+  return launch4<Wide128, false, false, false, W_GRAD>(p, s);
 }
 
 bool wide_narrow_tiles(const Geo& g) {
@@ -671,35 +776,50 @@ void wide_forward_shape(const Geo& g, int out[4]) {
   out[3] = sh.zchunks;
 }
 
+bool keep_fits(const Geo& g, const float* const* arrays, int n) {
+  if (g.sy % 4 || g.sz % 4 || g.org % 4) return false;
+  for (int i = 0; i < n; ++i)
+    if (!arrays[i] || !aligned16(arrays[i])) return false;
+  return true;
+}
+
+hipError_t launch_keep(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
+                       const float* q, const float* ex, const float* ey, const float* ez,
+                       const fd_source* src, const RecPlane* rp, float* keep, hipStream_t s) {
+  if (brick_grid(g)) return launch_keep_brick(g, c, up, u, un, q, ex, ey, ez, src, rp, keep, s);
+  P4 p = wide_args(g, c, up, u, un, q, ex, ey, ez, src, rp);
+  p.keep = keep;
+  if (wide_narrow_tiles(g)) {
+    if (ex) return launch4<Wide64, true, true, false, W_KEEP>(p, s);
+    return launch4<Wide64, false, true, false, W_KEEP>(p, s);
+  }
+  if (ex) return launch4<Wide128, true, true, false, W_KEEP>(p, s);
+  return launch4<Wide128, false, true, false, W_KEEP>(p, s);
+}
+
+hipError_t launch_acc(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
+                      const float* q, const float* ex, const float* ey, const float* ez,
+                      const RecPlane* rp, const float* s1, const float* s2, float* g_acc,
+                      hipStream_t s) {
+  if (brick_grid(g))
+    return launch_acc_brick(g, c, up, u, un, q, ex, ey, ez, rp, s1, s2, g_acc, s);
+  P4 p = wide_args(g, c, up, u, un, q, ex, ey, ez, nullptr, rp);
+  p.s1 = s1;
+  p.s2 = s2;
+  p.g_acc = g_acc;
+  if (wide_narrow_tiles(g)) {
+    if (ex) return launch4<Wide64, true, true, false, W_ACC>(p, s);
+    return launch4<Wide64, false, true, false, W_ACC>(p, s);
+  }
+  if (ex) return launch4<Wide128, true, true, false, W_ACC>(p, s);
+  return launch4<Wide128, false, true, false, W_ACC>(p, s);
+}
+
 hipError_t launch_forward_wide(const Geo& g, const Coef& c, const float* up, const float* u,
                                float* un, const float* q, const float* ex, const float* ey,
                                const float* ez, const fd_source* src, const float* const rin[2],
                                float* const sout[2], hipStream_t s, const RecPlane* rp) {
-  P4 p{};
-  p.g = g;
-  p.c = c;
-  p.u = u;
-  p.up = up;
-  p.q = q;
-  p.un = un;
-  p.ex = ex;
-  p.ey = ey;
-  p.ez = ez;
-  p.si = p.sj = p.sk = -1;
-  p.sw = 0.f;
-  p.rk = -1;
-  if (rp && rp->map) {
-    p.rmap = rp->map;
-    p.rk = rp->k;
-    p.rrow = rp->row;
-    p.radd = rp->add;
-  }
-  if (src) {
-    p.si = src->i;
-    p.sj = src->j;
-    p.sk = src->k;
-    p.sw = src->w;
-  }
+  P4 p = wide_args(g, c, up, u, un, q, ex, ey, ez, src, rp);
   const bool xch = rin != nullptr;
   if (xch) {
     for (int f = 0; f < 2; ++f) {

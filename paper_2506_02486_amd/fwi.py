@@ -7,11 +7,11 @@ gradient of the loss with respect to m, computed by
 
 * a forward sweep that keeps ``(u^{n-1}, u^n)`` every ``checkpoint_every`` steps
   (one native step loop, fd_forward_run, per checkpoint interval),
-* a reverse sweep over the segments, last first: each segment's wavefields are
-  recomputed from its checkpoint into a segment buffer, then for n descending the
-  adjoint step forms the adjoint field at n from those at n+1 and n+2 with the
-  gradient accumulation fused in, and the trace residual of step n-1 is added at
-  the receivers,
+* a reverse sweep over the segments, last first: each segment is recomputed from its
+  checkpoint, keeping s_n = L u^n + f^n of every step (fd_forward_keep), then for n
+  descending the adjoint step forms the adjoint field at n from those at n+1 and n+2,
+  with the gradient terms of the kept s_n and the trace residual of step n-1 added in
+  its launch (fd_adjoint_run),
 * the final scaling of the accumulated gradient to grad_m.
 
 The adjoint runs by default in the scaled variable b = vdt2 D lambda
@@ -33,14 +33,6 @@ import torch
 
 from . import api
 
-# grids up to this many points run short, latency-bound launches: there the receiver
-# residual is added in the adjoint update's own launch (fd_adjoint_step_scaled_res),
-# as it is on grids that run as bricks or on 16-byte lanes (they load the residual row
-# with their other operands); the marching kernel of one float per lane would wait for
-# its map lookup, and a separate launch costs less there
-SMALL_GRID_POINTS = 1 << 20
-
-
 class FWIProblem:
     """One shot of an FWI gradient: geometry, time axis, source, receivers."""
 
@@ -54,7 +46,7 @@ class FWIProblem:
         self.nt = int(nt)
         self.src = tuple(int(x) for x in src)
         self.device = device
-        # checkpoint_every = 0 keeps every state u^0 .. u^{nt-1} (nt volumes: 89 GB
+        # checkpoint_every = 0 keeps s_n = L u^n + f^n of every step (nt volumes: 89 GB
         # at 256^3 and 1000 steps fits one MI355X's 288 GB) and skips the recompute
         self.C = int(checkpoint_every)
         if self.C < 0:
@@ -73,7 +65,7 @@ class FWIProblem:
         self.m = g.zeros(device)
         self.vdt2 = g.zeros(device)
         self.ckpt: list[tuple[torch.Tensor, torch.Tensor]] = []
-        self.states: list[torch.Tensor] = []
+        self.kept: list[torch.Tensor] = []  # checkpoint_every = 0: s_0 .. s_{nt-1}
 
     # ------------------------------------------------------------ forward
     def set_model(self, m_interior: torch.Tensor):
@@ -90,8 +82,16 @@ class FWIProblem:
         traces = torch.zeros((self.nt, self.nrec), dtype=torch.float32, device=self.device)
         self.ckpt = []
         if checkpoints and self.C == 0:
-            return self._forward_store_all(traces)
-        self.states = []
+            if len(self.kept) != self.nt:
+                self.kept = []
+                torch.cuda.empty_cache()
+                self.kept = [torch.empty(g.elems, dtype=torch.float32, device=self.device)
+                             for _ in range(self.nt)]
+            api.forward_keep(g, up, u, un, self.vdt2, self.sponge, self.nt, self.kept,
+                             src=self.src, wavelet=self.w, rec_off=self.rec_off, traces=traces,
+                             rec_plane=self.rec_plane)
+            return traces
+        self.kept = []
         step = self.C if self.C > 0 else self.nt
         for s in range(0, self.nt, step):  # one native loop per checkpoint interval
             e = min(s + step, self.nt)
@@ -101,25 +101,6 @@ class FWIProblem:
                                         src=self.src, wavelet=self.w[s:e],
                                         rec_off=self.rec_off, traces=traces[s:e],
                                         rec_plane=self.rec_plane)
-        return traces
-
-    def _forward_store_all(self, traces: torch.Tensor) -> torch.Tensor:
-        """Forward sweep writing u^{n+1} of step n into its own buffer: states[n] is
-        u^n for n < nt (states[0] = u^0 = 0); u^{nt} lands in a spare buffer."""
-        g = self.grid
-        if len(self.states) != self.nt + 2:
-            self.states = []
-            torch.cuda.empty_cache()
-            self.states = [g.zeros(self.device) for _ in range(self.nt + 2)]
-        else:
-            self.states[0].zero_()
-            self.states[-1].zero_()
-        zero = self.states[-1]  # u^{-1}
-        for n in range(self.nt):
-            up = zero if n == 0 else self.states[n - 1]
-            api.step_fused(g, up, self.states[n], self.states[n + 1], self.vdt2, self.sponge,
-                           (self.src, float(self.w[n])))
-            api.record_receivers(g, self.states[n + 1], self.rec_off, traces[n])
         return traces
 
     # ------------------------------------------------------------ adjoint
@@ -136,7 +117,7 @@ class FWIProblem:
             raise ValueError("want_grad_w goes with scaled=True, want_lambda_src with False")
         g = self.grid
         nt, C = self.nt, self.C
-        if not self.ckpt and not (C == 0 and self.states):
+        if not self.ckpt and not (C == 0 and self.kept):
             raise RuntimeError("backward needs a forward run with checkpoints")
         res = res.to(device=self.device, dtype=torch.float32).contiguous()
         if res.shape != (nt, self.nrec):
@@ -147,15 +128,13 @@ class FWIProblem:
         B = g.zeros(self.device)  # lambda^{n+1}
         api.scatter_add(g, B, self.rec_off, res[nt - 1])
         gq = g.zeros(self.device)
-        seg = self._segment_buffers()
         lam_src = torch.zeros(nt, dtype=torch.float32, device=self.device) if want_lambda_src else None
-        for j in range(self._segments() - 1, -1, -1):
-            s, e, seg = self._recompute(j, seg)
+        for s, e, kept in self._segments():
             for n in range(e - 1, s - 1, -1):
                 if lam_src is not None:
                     api.record_receivers(g, B, self.src_off, lam_src[n:n + 1])
-                api.adjoint_step(g, A, B, A, self.vdt2, self.sponge, u_n=seg[n - s], g_vdt2=gq,
-                                 src=(self.src, float(self.w[n])))
+                api.grad_accumulate(g, B, kept[n - s], self.sponge, gq)
+                api.adjoint_step(g, A, B, A, self.vdt2, self.sponge)
                 if n >= 1:
                     api.scatter_add(g, A, self.rec_off, res[n - 1])
                 A, B = B, A
@@ -166,39 +145,27 @@ class FWIProblem:
             return out, lam_src
         return out
 
-    def _segments(self) -> int:
-        return 1 if self.C == 0 else len(self.ckpt)
-
-    def _segment_buffers(self) -> list[torch.Tensor]:
+    def _segments(self):
+        """The segments of the reverse sweep, last first: (s, e, kept) with kept[i] =
+        s_{s+i} for s <= s + i < e, stored by the forward sweep or recomputed from the
+        segment's checkpoint (into the same volumes for every segment)."""
         if self.C == 0:
-            return []
-        return [self.grid.zeros(self.device) for _ in range(min(self.C, self.nt))]
-
-    def _recompute(self, j: int, seg: list[torch.Tensor]):
-        """(s, e, buffers) with buffers[i] = u^{s+i} for segment j: the stored states,
-        or u^s .. u^{e-1} recomputed into ``seg`` from the segment's checkpoint."""
-        if self.C == 0:
-            return 0, self.nt, self.states
-        g, C = self.grid, self.C
-        s = j * C
-        e = min(s + C, self.nt)
-        prev, cur = self.ckpt[j]
-        seg[0].copy_(cur)
-        before = prev
-        for n in range(s, e - 1):
-            i = n - s
-            api.step_fused(g, before, seg[i], seg[i + 1], self.vdt2, self.sponge,
-                           (self.src, float(self.w[n])))
-            before = seg[i]
-        return s, e, seg
-
-    @property
-    def _inject_in_step(self) -> bool:
+            yield 0, self.nt, self.kept
+            return
         g = self.grid
-        if self.rec_plane is None:
-            return False
-        return (g.nx * g.ny * g.nz <= SMALL_GRID_POINTS or api.step_bricks(g)
-                or api.step_kernel(g)["kernel"] in ("wide_128x32", "wide_64x64"))
+        # only the interiors of the kept volumes are written and read; the wavefields'
+        # zero halos are the Dirichlet boundary
+        kept = [torch.empty(g.elems, dtype=torch.float32, device=self.device)
+                for _ in range(min(self.C, self.nt))]
+        field = [g.zeros(self.device) for _ in range(3)]
+        for j in range(len(self.ckpt) - 1, -1, -1):
+            s = j * self.C
+            e = min(s + self.C, self.nt)
+            for f, c in zip(field, self.ckpt[j]):
+                f.copy_(c)
+            api.forward_keep(g, *field, self.vdt2, self.sponge, e - s, kept, src=self.src,
+                             wavelet=self.w[s:e])
+            yield s, e, kept
 
     def _backward_scaled(self, res: torch.Tensor, want_grad_w: bool):
         g, nt = self.grid, self.nt
@@ -206,24 +173,13 @@ class FWIProblem:
         B = g.zeros(self.device)  # b^{n+1}
         api.scatter_add_scaled(g, B, self.rec_off, res[nt - 1], self.vdt2, self.sponge)
         gb = g.zeros(self.device)
-        seg = self._segment_buffers()
         grad_w = torch.zeros(nt, dtype=torch.float32, device=self.device) if want_grad_w else None
-        in_step = self._inject_in_step
-        for j in range(self._segments() - 1, -1, -1):
-            s, e, seg = self._recompute(j, seg)
-            for n in range(e - 1, s - 1, -1):
-                if grad_w is not None:
-                    api.record_receivers(g, B, self.src_off, grad_w[n:n + 1])
-                # the residual of step n-1 enters at the receivers: in the update's own
-                # launch when they share one plane (see SMALL_GRID_POINTS), else by a
-                # separate launch
-                inj = (self.rec_plane, res[n - 1]) if n >= 1 and in_step else None
-                api.adjoint_step_scaled(g, A, B, A, self.vdt2, self.sponge, u_n=seg[n - s],
-                                        g_b=gb, src=(self.src, float(self.w[n])), res=inj)
-                if n >= 1 and inj is None:
-                    api.scatter_add_scaled(g, A, self.rec_off, res[n - 1], self.vdt2,
-                                           self.sponge)
-                A, B = B, A
+        for s, e, kept in self._segments():
+            A, B = api.adjoint_run(g, A, B, self.vdt2, self.sponge, e - s, kept, gb,
+                                   rec_off=self.rec_off, res=res[s:e],
+                                   res0=res[s - 1] if s >= 1 else None, rec_plane=self.rec_plane,
+                                   w_off=self.src_off if want_grad_w else None,
+                                   w_out=grad_w[s:e] if want_grad_w else None)
         api.grad_finalize_scaled(g, gb, self.vdt2, self.dt, gb)
         out = g.interior(gb).clone()
         if want_grad_w:
