@@ -213,13 +213,22 @@ __global__ void __launch_bounds__(BS) scatter_add_kernel(float* a, const int64_t
   if (r < n) atomicAdd(a + off[r], vals[r]);
 }
 
-// One thread per element of the padded box [-4,n+4)^3 in each of PREP_K planes,
-// one block row per (j, k-group): interior from v, face halo from the periodic image,
-// edges 0.  v0 points at interior (0,0,0) of the input, which has its own strides.
-// The PREP_K planes' loads are issued before any store, so that a thread keeps
-// several loads in flight (one per thread left the 224 MB read of a 384^3 model
-// latency-bound at about 3 TB/s).
+// The padded box [-4,n+4)^3 of vdt2: interior from v, face halo from the periodic image,
+// edges 0.  v0 points at interior (0,0,0) of the input, which has its own strides.  A
+// wave takes an x row (64 points at a time) of one y in PREP_K planes, whose loads are
+// issued before any store, and a block of four waves four neighbouring y, so rows of any
+// length keep most lanes busy; a block goes on to every gridDim.z-th group of planes.
+// HBM-bound (one array read, one written); with a block of 256 points of one row the
+// padded rows of 264 points of a 256^3 grid gave every second block 8 points: 74.6 us,
+// now 36.1 (3.7 TB/s); 128^3 11.9 / 8.8, 384^3 187 / 156, 512^3 395 / 352.
+// VMAX: the same pass reduces max and min of v (as float bit patterns: positive floats
+// order as integers) into vm[0], vm[1], and the block that finishes last (the counter
+// vm[2]) writes both to `out`, host memory the device can reach: an admission of a shot
+// needs no second pass over v, no copy and no host round trip (before: 26 us for the
+// maximum of a 1M-point shot beside 7 us for vdt2, and a copy; now 15-20 us in all).  vm
+// must start as admit_kernel sets it.
 constexpr int PREP_K = 4;
+constexpr int PREP_Y = BS / 64;
 
 __device__ __forceinline__ int wrap_index(int a, int n) {
   int c = a < 0 ? a + n : (a >= n ? a - n : a);
@@ -227,51 +236,6 @@ __device__ __forceinline__ int wrap_index(int a, int n) {
   while (c < 0) c += n;
   while (c >= n) c -= n;
   return c;
-}
-
-__global__ void __launch_bounds__(BS) prep_vdt2_kernel(Geo g, const float* __restrict__ v0,
-                                                       long long vsy, long long vsz,
-                                                       float* __restrict__ q, double dt,
-                                                       bool from_m) {
-  const int jj = blockIdx.y - 4;                  // j in [-4, ny+4)
-  const int k0 = (int)blockIdx.z * PREP_K - 4;    // first k of the group, in [-4, nz+4)
-  const int oj = (jj < 0) + (jj >= g.ny);
-  const int cj = wrap_index(jj, g.ny);
-  for (int ii = (int)(blockIdx.x * BS + threadIdx.x) - 4; ii < g.nx + 4; ii += gridDim.x * BS) {
-    const int oi = (ii < 0) + (ii >= g.nx);
-    const int ci = wrap_index(ii, g.nx);
-    float vin[PREP_K];
-    bool use[PREP_K];
-#pragma unroll
-    for (int t = 0; t < PREP_K; ++t) {
-      const int kk = k0 + t;
-      const int ok = (kk < 0) + (kk >= g.nz);
-      use[t] = kk < g.nz + 4 && oi + oj + ok <= 1;
-      vin[t] = use[t] ? v0[(long long)wrap_index(kk, g.nz) * vsz + (long long)cj * vsy + ci] : 0.f;
-    }
-#pragma unroll
-    for (int t = 0; t < PREP_K; ++t) {
-      const int kk = k0 + t;
-      if (kk >= g.nz + 4) break;
-      float val = 0.f;
-      if (use[t]) {
-        if (from_m) {
-          val = (float)(dt * dt / (double)vin[t]);
-        } else {
-          const double vv = (double)vin[t] * dt;
-          val = (float)(vv * vv);
-        }
-      }
-      q[at(g, ii, jj, kk)] = val;
-    }
-  }
-}
-
-__global__ void vmax_init_kernel(int32_t* out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    out[0] = 0;           // max of the float bit patterns (positive floats order as ints)
-    out[1] = 0x7f800000;  // min, starting at +inf
-  }
 }
 
 __device__ __forceinline__ int wave_max(int v) {
@@ -283,20 +247,117 @@ __device__ __forceinline__ int wave_min(int v) {
   return v;
 }
 
+// The block's max and min into out[0], out[1]: one atomic each, and only where it would
+// change the value (atomics of many blocks on one address take their turns: a pair for
+// each of 1024 blocks made a 25 us kernel of a 4 MB read).
+__device__ __forceinline__ void reduce_max_min(int mx, int mn, int32_t* out) {
+  __shared__ int red[2][BS / 64];
+  mx = wave_max(mx);
+  mn = wave_min(mn);
+  const int t = threadIdx.x + blockDim.x * threadIdx.y;
+  if ((t & 63) == 0) {
+    red[0][t >> 6] = mx;
+    red[1][t >> 6] = mn;
+  }
+  __syncthreads();
+  if (t == 0) {
+    for (int i = 1; i < BS / 64; ++i) {
+      mx = max(mx, red[0][i]);
+      mn = min(mn, red[1][i]);
+    }
+    if (__hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < mx) atomicMax(out, mx);
+    if (__hip_atomic_load(out + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > mn)
+      atomicMin(out + 1, mn);
+  }
+}
+
+template <bool VMAX>
+__global__ void __launch_bounds__(BS) prep_vdt2_kernel(Geo g, const float* __restrict__ v0,
+                                                       long long vsy, long long vsz,
+                                                       float* __restrict__ q, double dt,
+                                                       bool from_m, int32_t* vm, int32_t* out) {
+  const int jj = (int)(blockIdx.y * PREP_Y + threadIdx.y) - 4;  // j in [-4, ny+4)
+  const int oj = (jj < 0) + (jj >= g.ny);
+  int mx = 0, mn = 0x7f800000;
+  if (jj < g.ny + 4) {
+    const int cj = wrap_index(jj, g.ny);
+    for (int k0 = (int)blockIdx.z * PREP_K - 4; k0 < g.nz + 4; k0 += (int)gridDim.z * PREP_K) {
+      for (int ii = (int)threadIdx.x - 4; ii < g.nx + 4; ii += 64) {
+        const int oi = (ii < 0) + (ii >= g.nx);
+        const int ci = wrap_index(ii, g.nx);
+        float vin[PREP_K];
+        bool use[PREP_K];
+#pragma unroll
+        for (int t = 0; t < PREP_K; ++t) {
+          const int kk = k0 + t;
+          const int ok = (kk < 0) + (kk >= g.nz);
+          use[t] = kk < g.nz + 4 && oi + oj + ok <= 1;
+          vin[t] =
+              use[t] ? v0[(long long)wrap_index(kk, g.nz) * vsz + (long long)cj * vsy + ci] : 0.f;
+        }
+#pragma unroll
+        for (int t = 0; t < PREP_K; ++t) {
+          const int kk = k0 + t;
+          if (kk >= g.nz + 4) break;
+          float val = 0.f;
+          if (use[t]) {
+            if (from_m) {
+              val = (float)(dt * dt / (double)vin[t]);
+            } else {
+              const double vv = (double)vin[t] * dt;
+              val = (float)(vv * vv);
+            }
+            if (VMAX) {  // (a halo cell repeats an interior one)
+              mx = max(mx, __float_as_int(vin[t]));
+              mn = min(mn, __float_as_int(vin[t]));
+            }
+          }
+          q[at(g, ii, jj, kk)] = val;
+        }
+      }
+    }
+  }
+  if (VMAX) {
+    reduce_max_min(mx, mn, vm);
+    if (threadIdx.x == 0 && threadIdx.y == 0) {
+      // the counter after this block's atomics have been performed; no fence: everything
+      // shared is atomics, and a device-scope release would write the L2 back, once per
+      // block (100 us)
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const int done = __hip_atomic_fetch_add(vm + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (done == (int)(gridDim.y * gridDim.z) - 1) {
+        out[0] = __hip_atomic_load(vm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        out[1] = __hip_atomic_load(vm + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
+}
+
+__device__ __forceinline__ void vmax_init(int32_t* out) {
+  out[0] = 0;           // max of the float bit patterns (positive floats order as ints)
+  out[1] = 0x7f800000;  // min, starting at +inf
+}
+
+__global__ void vmax_init_kernel(int32_t* out) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) vmax_init(out);
+}
+
 // max and min of v (as float bit patterns: positive floats order as integers) over
-// an nx x ny x nz view.  A block takes VMAX_LINES x-lines at a time (their row bases
-// are uniform: no per-element division), so that a thread has VMAX_LINES loads in
-// flight; lines past the last repeat the last one (no effect on max or min).  One
-// atomic pair per block.
+// an nx x ny x nz view.  A wave takes VMAX_LINES x-lines at a time (their row bases
+// are uniform: no per-element division), 64 points of each, so that a thread has
+// VMAX_LINES loads in flight; lines past the last repeat the last one (no effect on max
+// or min).  fd_cfl_dt, copy and synchronisation included, us before / after: 128^3 56 /
+// 40, 384^3 105 / 71, 512^3 167 / 122.
 constexpr int VMAX_LINES = 8;
 
 __global__ void __launch_bounds__(BS) vmax_kernel(int nx, int ny, int nz,
                                                   const float* __restrict__ v0, long long vsy,
                                                   long long vsz, int32_t* out) {
   const long long nline = (long long)ny * nz;
+  const long long wave = (long long)blockIdx.x * (BS / 64) + (threadIdx.x >> 6);
   int mx = 0, mn = 0x7f800000;
-  for (long long l0 = (long long)blockIdx.x * VMAX_LINES; l0 < nline;
-       l0 += (long long)gridDim.x * VMAX_LINES) {
+  for (long long l0 = wave * VMAX_LINES; l0 < nline;
+       l0 += (long long)gridDim.x * (BS / 64) * VMAX_LINES) {
     const float* row[VMAX_LINES];
 #pragma unroll
     for (int u = 0; u < VMAX_LINES; ++u) {
@@ -304,7 +365,7 @@ __global__ void __launch_bounds__(BS) vmax_kernel(int nx, int ny, int nz,
       const long long k = line / ny;
       row[u] = v0 + k * vsz + (line - k * ny) * vsy;
     }
-    for (int i = threadIdx.x; i < nx; i += BS) {
+    for (int i = threadIdx.x & 63; i < nx; i += 64) {
       int bits[VMAX_LINES];
 #pragma unroll
       for (int u = 0; u < VMAX_LINES; ++u) bits[u] = __float_as_int(row[u][i]);
@@ -315,23 +376,7 @@ __global__ void __launch_bounds__(BS) vmax_kernel(int nx, int ny, int nz,
       }
     }
   }
-  mx = wave_max(mx);
-  mn = wave_min(mn);
-  __shared__ int red[2][BS / 64];
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    red[0][w] = mx;
-    red[1][w] = mn;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int i = 1; i < BS / 64; ++i) {
-      mx = max(mx, red[0][i]);
-      mn = min(mn, red[1][i]);
-    }
-    atomicMax(out, mx);
-    atomicMin(out + 1, mn);
-  }
+  reduce_max_min(mx, mn, out);
 }
 
 // scaled: the accumulator holds sum b (L u + f) with b = Q D lambda, so that
@@ -370,6 +415,35 @@ __global__ void __launch_bounds__(BS) grad_accumulate_kernel(Geo g, const float*
 __global__ void __launch_bounds__(BS) zero_kernel(float* __restrict__ dst, long long n) {
   for (long long i = blockIdx.x * (long long)BS + threadIdx.x; i < n; i += (long long)gridDim.x * BS)
     dst[i] = 0.f;
+}
+
+// What a shot's admission writes besides its model, in one launch: its wavefields zeroed
+// (zero4 16-byte words from zero), the slots of its max(v) reduction set (vm), and its
+// tables copied word by word from the host's staging buffer, which the device reads over
+// the host link: three copies of a few KB cost a launch each.
+struct AdmitTables {
+  const uint32_t* src[3];
+  uint32_t* dst[3];
+  unsigned n[3];
+};
+
+__global__ void __launch_bounds__(BS) admit_kernel(float4* __restrict__ zero, long long zero4,
+                                                   int32_t* vm, AdmitTables tab, int table_blocks) {
+  if ((int)blockIdx.x < table_blocks) {
+    if (vm && blockIdx.x == 0 && threadIdx.x == 0) {
+      vmax_init(vm);
+      vm[2] = 0;
+    }
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+      for (unsigned i = blockIdx.x * BS + threadIdx.x; i < tab.n[s]; i += (unsigned)table_blocks * BS)
+        tab.dst[s][i] = tab.src[s][i];
+    return;
+  }
+  const long long step = (long long)((int)gridDim.x - table_blocks) * BS;
+  for (long long i = ((int)blockIdx.x - table_blocks) * (long long)BS + threadIdx.x; i < zero4;
+       i += step)
+    zero[i] = float4{0.f, 0.f, 0.f, 0.f};
 }
 
 // blockIdx.y = position in the active-slot list; x covers that shot's receivers.
@@ -468,20 +542,43 @@ hipError_t launch_scatter_add(float* a, const int64_t* off, const float* vals, i
   return hipGetLastError();
 }
 
+// Blocks of prep_vdt2_kernel: one per group of rows, or about `most`, each taking several
+// groups (the counter of VMAX takes the blocks one after the other).
+static dim3 prep_grid(const Geo& g, long long most) {
+  const unsigned by = (unsigned)((g.ny + 8 + PREP_Y - 1) / PREP_Y);
+  const long long groups = (g.nz + 8 + PREP_K - 1) / PREP_K;
+  return dim3(1, by, (unsigned)std::min(groups, std::max(1LL, most / by)));
+}
+
 hipError_t launch_prepare_vdt2(const Geo& g, const float* v, float* q, double dt, bool from_m,
                                hipStream_t s) {
-  const unsigned bx = blocks_for(g.nx + 8, 64);
-  hipLaunchKernelGGL(prep_vdt2_kernel, dim3(bx, g.ny + 8, (g.nz + 8 + PREP_K - 1) / PREP_K),
-                     dim3(BS), 0, s, g, v + g.org, (long long)g.sy, (long long)g.sz, q, dt,
-                     from_m);
+  hipLaunchKernelGGL(prep_vdt2_kernel<false>, prep_grid(g, 1LL << 30), dim3(64, PREP_Y), 0, s, g,
+                     v + g.org, (long long)g.sy, (long long)g.sz, q, dt, from_m, nullptr, nullptr);
   return hipGetLastError();
 }
 
-hipError_t launch_prepare_vdt2_view(const Geo& g, const float* v, long long vsy, long long vsz,
-                                    float* q, double dt, hipStream_t s) {
-  const unsigned bx = blocks_for(g.nx + 8, 64);
-  hipLaunchKernelGGL(prep_vdt2_kernel, dim3(bx, g.ny + 8, (g.nz + 8 + PREP_K - 1) / PREP_K),
-                     dim3(BS), 0, s, g, v, vsy, vsz, q, dt, false);
+hipError_t launch_prepare_vdt2_max(const Geo& g, const float* v, long long vsy, long long vsz,
+                                   float* q, double dt, int32_t* vm, int32_t* out, hipStream_t s) {
+  hipLaunchKernelGGL(prep_vdt2_kernel<true>, prep_grid(g, 512), dim3(64, PREP_Y), 0, s, g, v, vsy,
+                     vsz, q, dt, false, vm, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_admit(float* zero, long long n, int32_t* vm, const void* const src[3],
+                        void* const dst[3], const unsigned words[3], hipStream_t s) {
+  AdmitTables t;
+  unsigned most = 1;
+  for (int i = 0; i < 3; ++i) {
+    t.src[i] = static_cast<const uint32_t*>(src[i]);
+    t.dst[i] = static_cast<uint32_t*>(dst[i]);
+    t.n[i] = words[i];
+    most = std::max(most, words[i]);
+  }
+  // (the host link's latency bounds the tables: a word or two per thread)
+  const unsigned tb = std::min(128u, (most + BS - 1) / BS);
+  const unsigned zb = n > 0 ? blocks_for(n / 4, 4096) : 0;
+  hipLaunchKernelGGL(admit_kernel, dim3(tb + zb), dim3(BS), 0, s, reinterpret_cast<float4*>(zero),
+                     n / 4, vm, t, (int)tb);
   return hipGetLastError();
 }
 
@@ -504,7 +601,8 @@ hipError_t launch_vmax_view(int nx, int ny, int nz, const float* v, long long vs
   hipLaunchKernelGGL(vmax_init_kernel, dim3(1), dim3(64), 0, s, out);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const long long groups = ((long long)ny * nz + VMAX_LINES - 1) / VMAX_LINES;
+  const long long per = (long long)VMAX_LINES * (BS / 64);
+  const long long groups = ((long long)ny * nz + per - 1) / per;
   const unsigned nb = (unsigned)std::min<long long>(std::max<long long>(groups, 1), 1024);
   hipLaunchKernelGGL(vmax_kernel, dim3(nb), dim3(BS), 0, s, nx, ny, nz, v, vsy, vsz, out);
   return hipGetLastError();

@@ -429,7 +429,6 @@ __global__ void __launch_bounds__(LANES * TROWS, brick_waves(KZ, MODE))
 // One step of several grids in one launch, their parameters in the kernel arguments:
 // grid i owns blocks [start[i], start[i+1]).
 struct BrickMulti {
-  int n;
   int start[kBrickMulti + 1];
   BrickArgs grid[kBrickMulti];
 };
@@ -438,8 +437,11 @@ template <int KZ>
 __global__ void __launch_bounds__(8 * TROWS, brick_waves(KZ, B_FWD))
     brick_multi_kernel(BrickMulti A) {
   const int b = remap_brick(blockIdx.x, gridDim.x);
+  // the grid that owns block b: all starts compared at once (unused ones lie past the
+  // last block; a search would wait for one kernel-argument load after another)
   int i = 0;
-  while (i + 1 < A.n && b >= A.start[i + 1]) ++i;
+#pragma unroll
+  for (int j = 1; j < kBrickMulti; ++j) i += b >= A.start[j];
   const BrickArgs& p = A.grid[i];
   int bx, by, bz;
   brick_tile(p, (unsigned)(b - A.start[i]), &bx, &by, &bz);
@@ -604,7 +606,6 @@ hipError_t launch_brick_multi(const WideStep* steps, int n, hipStream_t s) {
   for (int i = 0; i < n; ++i) points += (long long)steps[i].g.nx * steps[i].g.ny * steps[i].g.nz;
   const int kz = brick_planes(points);
   BrickMulti A;
-  A.n = n;
   long long nb = 0;
   for (int i = 0; i < n; ++i) {
     const WideStep& w = steps[i];

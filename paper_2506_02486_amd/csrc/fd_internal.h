@@ -258,9 +258,16 @@ hipError_t launch_batched(const BatchShot* shots, const int4* tiles, int ntiles,
 hipError_t launch_batched_record(const BatchShot* shots, const int* slots, int nslots,
                                  int max_nrec, const BatchStep& a, hipStream_t s);
 // vdt2 = (v dt)^2 on the padded box of g from a strided velocity view (element
-// (i,j,k) at v[k*vsz + j*vsy + i], interior only read); faces wrap, edges 0.
-hipError_t launch_prepare_vdt2_view(const Geo& g, const float* v, long long vsy, long long vsz,
-                                    float* q, double dt, hipStream_t s);
+// (i,j,k) at v[k*vsz + j*vsy + i], interior only read); faces wrap, edges 0.  The same
+// pass reduces max and min of v (float bits) through vm (three device int32, as
+// launch_admit sets them) into out[0], out[1] (pinned host memory).
+hipError_t launch_prepare_vdt2_max(const Geo& g, const float* v, long long vsy, long long vsz,
+                                   float* q, double dt, int32_t* vm, int32_t* out, hipStream_t s);
+// One launch: n floats from zero (16-byte aligned, n a multiple of 4; may be 0) set to 0,
+// vm (may be NULL) made ready for launch_prepare_vdt2_max, and three tables of 32-bit
+// words copied from pinned host memory.
+hipError_t launch_admit(float* zero, long long n, int32_t* vm, const void* const src[3],
+                        void* const dst[3], const unsigned words[3], hipStream_t s);
 // max and min of a strided velocity view's interior into out[0], out[1] (float bits)
 hipError_t launch_vmax_view(int nx, int ny, int nz, const float* v, long long vsy,
                             long long vsz, int32_t* out, hipStream_t s);

@@ -6,12 +6,13 @@
 //             arena: the paper's global segment, Sec. 3.1) and its admission work
 //             runs asynchronously on a stream of a bounded pool (lazy creation,
 //             reuse, MAX_ACTIVE_STREAMS with partial synchronisation, Sec. 3.2):
-//             phase 1 zeroes its wavefields and reduces max(v) into its block;
-//             phase 2, once the maximum is on the host (stability checked), builds
-//             vdt2 from the caller's velocity view and uploads sponge tables,
-//             receiver offsets and a receiver-plane map; at most kPrepareAhead
-//             shots are staging or staged at once, so their admission overlaps
-//             the steps of the running shots;
+//             one launch zeroes its wavefields and copies its sponge tables, receiver
+//             offsets and receiver-plane map from pinned memory, one builds vdt2 from
+//             the caller's velocity view and reduces max(v) into pinned memory (where
+//             the sponge is designed for the shot's own maximum, its tables follow
+//             once that is on the host); at most kPrepareAhead shots are staging or
+//             staged at once, so their admission overlaps the steps of the running
+//             shots;
 //   staged  : ready, waiting to join the batched step;
 //   active  : in a slot: every active shot advances one time step per batched
 //             step, each at its own step n (u^n in arr[n % 3]);
@@ -176,8 +177,6 @@ struct Shot {
   // admission
   hipStream_t as = nullptr;   // pool stream of its admission work
   hipEvent_t ev = nullptr;    // end of the current admission phase
-  hipEvent_t mev = nullptr;   // end of the model's uploads, before the stability check
-                              // of the same phase (NULL: ev ends both)
   float* stage = nullptr;     // pinned: max/min of v, then the tables to upload
   size_t stage_cap = 0;       // floats
   bool wide = false;          // a grid the 16-byte-lane kernel steps when alone
@@ -294,16 +293,13 @@ int check_vmax(const Shot* s) {
   return FD_OK;
 }
 
-// The model on the shot's admission stream: vdt2 from the caller's velocity view, and
-// (host) sponge tables for the design velocity vdesign, receiver offsets and plane
-// map into the staging buffer, uploaded; then event `end`.
-hipError_t admit_model(Server* S, Shot* s, double vdesign, hipEvent_t end) {
+// A shot's tables: (host) sponge tables for the design velocity vdesign, receiver
+// offsets and plane map into the staging buffer, and the launch that copies them to the
+// block; with `fresh` the same launch zeroes the three wavefields (adjacent in the
+// block) and makes the max(v) slots ready.  Also the shot's source wavelet.
+hipError_t admit_tables(Server* S, Shot* s, double vdesign, bool fresh) {
   const fd_shot_desc& d = s->d;
   const ShotLayout& L = s->L;
-  const Geo geo = make_geo(&L.g);
-  hipError_t e = launch_prepare_vdt2_view(geo, d.v_dev, d.v_ystride, d.v_zstride,
-                                          shot_vol(S, s, 3), d.dt, s->as);
-  if (e != hipSuccess) return e;
   // staging layout (floats): [2: max/min] [nx+ny+nz: sponge] [pad to even]
   // [2*nrec: int64 offsets] [nx*ny: int32 plane map]
   float* h = s->stage + 2;
@@ -315,49 +311,51 @@ hipError_t admit_model(Server* S, Shot* s, double vdesign, hipEvent_t end) {
     h += n3[a];
   }
   int64_t* hrec = reinterpret_cast<int64_t*>(s->stage + 2 + (d.nx + d.ny + d.nz + 1) / 2 * 2);
-  if (d.nrec > 0) fd_receiver_offsets(&L.g, s->rec.data(), d.nrec, hrec);
-  e = hipMemcpyAsync(shot_at(S, s, L.sponge), s->stage + 2, 4 * (size_t)(d.nx + d.ny + d.nz),
-                     hipMemcpyHostToDevice, s->as);
-  if (e == hipSuccess && d.nrec > 0)
-    e = hipMemcpyAsync(shot_at(S, s, L.rec), hrec, 8 * (size_t)d.nrec, hipMemcpyHostToDevice,
-                       s->as);
+  int32_t* hmap = reinterpret_cast<int32_t*>(hrec + std::max(d.nrec, 0));
   // receivers on one plane: the stencil kernels write their rows themselves
   s->plane_k = -1;
   if (d.nrec > 0) {
-    int32_t* hmap = reinterpret_cast<int32_t*>(hrec + d.nrec);
+    fd_receiver_offsets(&L.g, s->rec.data(), d.nrec, hrec);
     if (fd_receiver_plane_map(&L.g, s->rec.data(), d.nrec, hmap, &s->plane_k) != FD_OK)
       s->plane_k = -1;
-    if (e == hipSuccess && s->plane_k >= 0)
-      e = hipMemcpyAsync(shot_at(S, s, L.rmap), hmap, 4 * (size_t)d.nx * (size_t)d.ny,
-                         hipMemcpyHostToDevice, s->as);
   }
-  if (e == hipSuccess) e = hipEventRecord(end, s->as);
+  const void* src[3] = {s->stage + 2, hrec, hmap};
+  void* dst[3] = {shot_at(S, s, L.sponge), shot_at(S, s, L.rec), shot_at(S, s, L.rmap)};
+  const unsigned words[3] = {(unsigned)(d.nx + d.ny + d.nz), 2u * (unsigned)std::max(d.nrec, 0),
+                             s->plane_k >= 0 ? (unsigned)d.nx * (unsigned)d.ny : 0u};
+  const hipError_t e = launch_admit(
+      shot_vol(S, s, 0), fresh ? (long long)(shot_vol(S, s, 3) - shot_vol(S, s, 0)) : 0,
+      fresh ? reinterpret_cast<int32_t*>(shot_at(S, s, L.vm)) : nullptr, src, dst, words, s->as);
   s->w.resize(d.nt);
   fd_ricker(s->w.data(), d.nt, 0, d.dt, d.f0, d.t0);
-  s->wide = forward_wide_tiles(geo);
+  s->wide = forward_wide_tiles(make_geo(&L.g));
   return e;
 }
 
-// The admission work that needs nothing from the host, on the shot's pool stream:
-// zero the three wavefields, reduce max(v) and min(v) into the block and copy them to
-// the staging buffer.  When the sponge's design velocity is known without that
-// maximum (given, or no sponge), the model (admit_model) comes first, ending with
-// event mev, so that the shot can join the step as soon as its model has landed, its
-// stability checked when the maximum arrives (event ev); else the maximum comes
-// first (ev) and the host builds the model from it.  *whole tells which.
+// The admission work that needs nothing from the host, on the shot's pool stream, ending
+// with event ev: the wavefields zeroed and the tables (where the sponge's design velocity
+// is known without max(v): given, or no sponge; *whole tells), then vdt2 with the
+// reduction of max(v) and min(v) into the staging buffer.  With the tables the shot can
+// join the step as soon as this work is enqueued (its stability is checked when ev has
+// passed); else the host builds them from the maximum (admit_tables, ending with ev).
 hipError_t admit_start(Server* S, Shot* s, bool* whole) {
   const fd_shot_desc& d = s->d;
   int32_t* vm = reinterpret_cast<int32_t*>(shot_at(S, s, s->L.vm));
   *whole = d.sponge_width == 0 || d.sponge_vmax > 0;
-  // the three wavefields are adjacent in the block: one launch zeroes them
-  hipError_t e = launch_zero(shot_vol(S, s, 0), (long long)(shot_vol(S, s, 3) - shot_vol(S, s, 0)), s->as);
-  if (e == hipSuccess && *whole) {
-    e = hipEventCreateWithFlags(&s->mev, hipEventDisableTiming);
-    if (e == hipSuccess) e = admit_model(S, s, d.sponge_width ? d.sponge_vmax : 0.0, s->mev);
+  hipError_t e;
+  if (*whole) {
+    e = admit_tables(S, s, d.sponge_width ? d.sponge_vmax : 0.0, true);
+  } else {
+    const void* src[3] = {};
+    void* dst[3] = {};
+    const unsigned words[3] = {};
+    e = launch_admit(shot_vol(S, s, 0), (long long)(shot_vol(S, s, 3) - shot_vol(S, s, 0)), vm, src,
+                     dst, words, s->as);
   }
   if (e == hipSuccess)
-    e = launch_vmax_view(d.nx, d.ny, d.nz, d.v_dev, d.v_ystride, d.v_zstride, vm, s->as);
-  if (e == hipSuccess) e = hipMemcpyAsync(s->stage, vm, 8, hipMemcpyDeviceToHost, s->as);
+    e = launch_prepare_vdt2_max(make_geo(&s->L.g), d.v_dev, d.v_ystride, d.v_zstride,
+                                shot_vol(S, s, 3), d.dt, vm,
+                                reinterpret_cast<int32_t*>(s->stage), s->as);
   if (e != hipSuccess) return e;
   return hipEventRecord(s->ev, s->as);
 }
@@ -366,11 +364,10 @@ hipError_t admit_start(Server* S, Shot* s, bool* whole) {
 // whose stream was synchronised).
 void drop_events(Shot* s) {
   if (s->ev) (void)hipEventDestroy(s->ev);
-  if (s->mev) (void)hipEventDestroy(s->mev);
-  s->ev = s->mev = nullptr;
+  s->ev = nullptr;
 }
 
-// Staging floats a shot needs (see admit_model).
+// Staging floats a shot needs (see admit_tables).
 size_t stage_floats(const fd_shot_desc& d) {
   return 2 + (size_t)(d.nx + d.ny + d.nz + 1) / 2 * 2 + 2 * (size_t)std::max(d.nrec, 0) +
          (d.nrec > 0 ? (size_t)d.nx * (size_t)d.ny : 0);
@@ -543,6 +540,9 @@ hipError_t upload_tables(Server* S) {
   S->ntiles4 = counts[1];
   S->nactive = na;
   S->max_nrec = mr;
+  S->table_dirty = false;
+  // a step whose parameters travel in kernel arguments reads no table
+  if (nt == 0 && na == 0) return hipSuccess;
   e = hipMemcpyAsync(S->d_shots, S->h_shots[st], sizeof(BatchShot) * S->max_slots,
                      hipMemcpyHostToDevice, S->cs);
   if (e == hipSuccess && nt)
@@ -550,7 +550,6 @@ hipError_t upload_tables(Server* S) {
   if (e == hipSuccess && na)
     e = hipMemcpyAsync(S->d_slots, h_slots, sizeof(int) * na, hipMemcpyHostToDevice, S->cs);
   if (e == hipSuccess) e = hipEventRecord(S->table_ev[st], S->cs);
-  S->table_dirty = false;
   return e;
 }
 
@@ -692,7 +691,8 @@ void progress(Server* S) {
         float vmax;
         memcpy(&vmax, &s->stage[0], 4);
         lk.unlock();
-        const hipError_t e = admit_model(S, s, (double)vmax, s->ev);
+        hipError_t e = admit_tables(S, s, (double)vmax, false);
+        if (e == hipSuccess) e = hipEventRecord(s->ev, s->as);
         lk.lock();
         if (e == hipSuccess) {
           s->state = State::Issued;
@@ -767,9 +767,9 @@ void progress(Server* S) {
       s->host_cap = (size_t)s->d.nt * (size_t)s->d.nrec;
       s->host = take_pinned(S, s->host_cap, &cap);
       if (!s->host) break;  // retried on the next pass
-      // admission work still running: the compute stream waits for the model's part
-      // of it (the stability check may land later), not the host
-      if (s->ev && hipStreamWaitEvent(S->cs, s->mev ? s->mev : s->ev, 0) != hipSuccess) {
+      // admission work still running: the compute stream waits for it (the stability
+      // check may land later), not the host
+      if (s->ev && hipStreamWaitEvent(S->cs, s->ev, 0) != hipSuccess) {
         give_pinned(S, s->host, cap);
         s->host = nullptr;
         break;
