@@ -702,7 +702,9 @@ class Simulation:
           record_receivers as separate calls;
         * ``"native"`` / ``"native-fused"``: the exchange / fused sequence looped in
           the library (fd_forward_run).
-        All give the same bits."""
+        All give the same bits, and the first two run as the library's loops too (a step
+        called from here costs 29 us of host time, more than a 200^3 step takes), unless
+        ``traces`` has a layout that only single rows of can be written."""
         if mode not in self.MODES:
             raise ValueError(f"mode must be one of {self.MODES}")
         g = self.grid
@@ -714,8 +716,11 @@ class Simulation:
             w = ricker(nt, self.dt, geom.f0, geom.t0, n0=self.n)
         if mode != "separate" and self.exchange and not self._faces_current:
             halo_pack(g, self.u, self.send, stream)
-        if mode.startswith("native"):
-            return self._run_native(nt, w, traces, stream, mode == "native")
+        whole = (self.rec_off is None
+                 or (traces.dim() == 2 and traces.is_contiguous() and traces.shape[0] >= nt
+                     and traces.shape[1] == self.nrec))
+        if mode.startswith("native") or (whole and mode in ("exchange", "fused")):
+            return self._run_native(nt, w, traces, stream, mode in ("native", "exchange"))
         for s in range(nt):
             src = None if w is None else (geom.src, float(w[s]))
             if mode == "exchange":
