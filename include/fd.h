@@ -129,11 +129,14 @@ int fd_set_kchunk(int32_t kchunk);
 
 /* Performance knob: tile shape of the forward stencil kernels (fd_step,
  * fd_step_fused, fd_step_exchange, fd_forward_run, fd_adjoint_step_scaled):
- * 0 = automatic: grids of more than 2^18 and at most 12.5 million points, whose
- * arrays stay in cache between steps, run as bricks (fd_step_bricks tells which):
- * forward updates, fd_step_exchange / fd_forward_run with all twelve face buffers
- * (nx a multiple of 4; the faces then read and written in that one launch), and
- * gradient passes (of smaller grids too); strides, origin and buffers 16-byte
+ * 0 = automatic: grids of more than 0.45 million points (rows rounded up to 64)
+ * and, in a run, at most 14.5 million, whose arrays stay in cache between steps, run
+ * as bricks (fd_step_bricks tells which): forward updates, fd_step_exchange /
+ * fd_forward_run with all twelve face buffers (0.55 to 12.5 million points, nx a
+ * multiple of 4; the faces then read and written in that one launch), and gradient
+ * passes (up to 12.5 million points; small grids too); single updates (fd_step,
+ * fd_step_fused, fd_adjoint_step_scaled, and fd_step_exchange where nx is a multiple
+ * of 128) of at most 2^22 points; strides, origin and buffers 16-byte
  * aligned.  Where bricks do not apply: a forward update that takes no faces inside
  * the kernel -- fd_step, fd_step_fused, fd_forward_run without a second face set,
  * fd_adjoint_step_scaled(_res) -- runs one thread per point on grids of at most
@@ -178,7 +181,7 @@ enum {
   FD_KERNEL_WIDE_64x64 = 4    /* the same with 64 x 64 tiles (ragged x extents) */
 };
 int fd_step_kernel(const fd_grid* g, int32_t with_faces, int32_t out[6]);
-/* 1 if a step over g (with_faces as for fd_step_kernel, arrays and buffers 16-byte
+/* 1 if a run's step over g (with_faces as for fd_step_kernel, arrays and buffers 16-byte
  * aligned) runs as bricks, 0 if fd_step_kernel's kernel steps it; FD_EINVAL for a bad
  * grid.  Host only. */
 int fd_step_bricks(const fd_grid* g, int32_t with_faces);

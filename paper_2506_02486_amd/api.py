@@ -401,7 +401,7 @@ def step_kernel(grid: Grid, faces: bool = False) -> dict:
 
 
 def step_bricks(grid: Grid, faces: bool = False) -> bool:
-    """Whether a step over ``grid`` runs as bricks (fd_step_bricks): the grids that the
+    """Whether a run's step over ``grid`` goes as bricks (fd_step_bricks): the grids that the
     caches hold between steps."""
     return bool(check(lib().fd_step_bricks(grid.ref, int(bool(faces))), "fd_step_bricks"))
 

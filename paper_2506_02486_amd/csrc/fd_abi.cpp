@@ -101,13 +101,14 @@ bool overlaps(const fd_grid* g, const float* a, const float* b) {
 
 // The forward update with no faces inside the kernel: bricks or the one-thread-per-point
 // kernel on grids small enough to stay in cache, else the z-marching kernel (the
-// same bits whichever runs).
+// same bits whichever runs).  most: up to how many points bricks (kBrickPoints...).
 hipError_t forward_update(const Geo& geo, const Coef& c, const float* up, const float* u,
                           float* un, const float* q, const float* ex, const float* ey,
                           const float* ez, const fd_source* src, hipStream_t s,
-                          const RecPlane* rp = nullptr) {
+                          const RecPlane* rp, long long most) {
   const float* const arrs[4] = {up, u, un, q};
-  if (brick_takes(geo, arrs)) return launch_brick(geo, c, up, u, un, q, ex, ey, ez, src, rp, s);
+  if (brick_takes(geo, arrs, most))
+    return launch_brick(geo, c, up, u, un, q, ex, ey, ez, src, rp, s);
   if (point_kernel_pays(geo)) return launch_step_point(geo, c, up, u, un, q, ex, ey, ez, src, rp, s);
   return launch_step(geo, c, up, u, un, q, ex, ey, ez, src, s, rp);
 }
@@ -265,8 +266,7 @@ int fd_step_bricks(const fd_grid* g, int32_t with_faces) {
   int rc = check_grid(g);
   if (rc) return rc;
   const Geo geo = make_geo(g);
-  return brick_grid(geo) && (long long)geo.nx * geo.ny * geo.nz > kBrickLeastPoints &&
-         (!with_faces || (geo.nx % 4 == 0 && geo.ny >= 4 && geo.nz >= 4));
+  return brick_step(geo, with_faces != 0, with_faces ? kBrickPointsMore : kBrickPoints);
 }
 
 namespace {
@@ -406,7 +406,7 @@ int fd_step(const fd_grid* g, const float* u_prev, const float* u, float* u_next
   rc = check_sponge(sp, &ex, &ey, &ez);
   if (rc) return rc;
   return check_hip(forward_update(make_geo(g), make_coef(g), u_prev, u, u_next, vdt2, ex, ey, ez,
-                                  nullptr, as_stream(stream)),
+                                  nullptr, as_stream(stream), nullptr, kBrickPointsOnce),
                    "fd_step launch");
 }
 
@@ -453,7 +453,8 @@ int fd_step_fused(const fd_grid* g, const float* u_prev, const float* u, float* 
   if (rc) return rc;
   const Geo geo = make_geo(g);
   hipStream_t s = as_stream(stream);
-  rc = check_hip(forward_update(geo, make_coef(g), u_prev, u, u_next, vdt2, ex, ey, ez, src, s),
+  rc = check_hip(forward_update(geo, make_coef(g), u_prev, u, u_next, vdt2, ex, ey, ez, src, s,
+                                nullptr, kBrickPointsOnce),
                  "fd_step_fused launch");
   if (rc || !face_out) return rc;
   return check_hip(launch_pack(geo, u_next, face_out, s), "fd_step_fused pack launch");
@@ -480,14 +481,16 @@ static hipError_t step_exchange(const Geo& geo, const Coef& c, const float* up, 
                                 float* un, const float* q, const float* ex, const float* ey,
                                 const float* ez, const fd_source* src,
                                 const float* const face_in[6], float* const face_out[6],
-                                hipStream_t s, const int64_t* rec_off = nullptr, int nrec = 0,
-                                float* row = nullptr, const int32_t* rec_map = nullptr,
-                                int rec_k = -1) {
+                                hipStream_t s, bool once, const int64_t* rec_off = nullptr,
+                                int nrec = 0, float* row = nullptr,
+                                const int32_t* rec_map = nullptr, int rec_k = -1) {
   hipError_t e = hipSuccess;
   bool all12 = face_in && face_out;
   for (int f = 0; f < 6 && all12; ++f) all12 = face_in[f] && face_out[f];
   const float* const arrs[4] = {up, u, un, q};
-  const bool bricks = all12 && brick_takes(geo, arrs, face_in, face_out);
+  // a single call keeps the marching kernel where its 128-wide tiles are full
+  const long long most = once && geo.nx % 128 == 0 ? kBrickPointsOnce : kBrickPointsMore;
+  const bool bricks = all12 && brick_takes(geo, arrs, most, face_in, face_out);
   if (bricks || (all12 && point_exchange_pays(geo))) {  // the whole step in one launch
     const RecPlane rp{rec_map, rec_k, row};
     const bool in_kernel = rec_map && nrec > 0;
@@ -515,7 +518,9 @@ static hipError_t step_exchange(const Geo& geo, const Coef& c, const float* up, 
     return e;
   }
   if (face_in) e = launch_unpack(geo, u, face_in, s);
-  if (e == hipSuccess) e = forward_update(geo, c, up, u, un, q, ex, ey, ez, src, s);
+  if (e == hipSuccess)
+    e = forward_update(geo, c, up, u, un, q, ex, ey, ez, src, s, nullptr,
+                       once ? kBrickPointsOnce : kBrickPointsMore);
   if (e == hipSuccess && face_out) e = launch_pack_record(geo, un, face_out, rec_off, nrec, row, s);
   else if (e == hipSuccess && nrec > 0) e = launch_record(un, rec_off, nrec, row, s);
   return e;
@@ -553,7 +558,7 @@ int fd_step_exchange(const fd_grid* g, const float* u_prev, float* u, float* u_n
   rc = check_sponge(sp, &ex, &ey, &ez);
   if (rc) return rc;
   return check_hip(step_exchange(make_geo(g), make_coef(g), u_prev, u, u_next, vdt2, ex, ey, ez,
-                                 src, face_in, face_out, as_stream(stream)),
+                                 src, face_in, face_out, as_stream(stream), true),
                    "fd_step_exchange launch");
 }
 
@@ -637,7 +642,7 @@ static hipError_t forward_steps(const fd_grid* g, fd_run* run, int nsend, int ns
     // with a receiver plane map and no faces by the stencil launch itself
     float* row = run->nrec ? run->traces + (int64_t)n * run->nrec : nullptr;
     if (nsend2) {
-      e = step_exchange(geo, c, up, u, un, run->vdt2, ex, ey, ez, sp_src, recv, nxt, s,
+      e = step_exchange(geo, c, up, u, un, run->vdt2, ex, ey, ez, sp_src, recv, nxt, s, false,
                         run->rec_off, run->nrec, row, run->rec_map, run->rec_k);
       float** t = cur;
       cur = nxt;
@@ -650,11 +655,12 @@ static hipError_t forward_steps(const fd_grid* g, fd_run* run, int nsend, int ns
       const float* const arrs[4] = {up, u, un, run->vdt2};
       const bool in_kernel = run->rec_map && run->nrec > 0 && !nsend &&
                              (receiver_plane_pays(geo) || point_kernel_pays(geo) ||
-                              brick_takes(geo, arrs) || wide_takes_step(geo, arrs));
+                              brick_takes(geo, arrs, kBrickPoints) ||
+                              wide_takes_step(geo, arrs));
       if (nsend) e = launch_unpack(geo, u, recv, s);
       if (e == hipSuccess)
         e = forward_update(geo, c, up, u, un, run->vdt2, ex, ey, ez, sp_src, s,
-                           in_kernel ? &rp : nullptr);
+                           in_kernel ? &rp : nullptr, nsend ? kBrickPointsMore : kBrickPoints);
       if (e == hipSuccess && nsend)
         e = launch_pack_record(geo, un, cur, run->rec_off, run->nrec, row, s);
       else if (e == hipSuccess && run->nrec && !in_kernel)
@@ -779,7 +785,8 @@ int fd_adjoint_run(const fd_grid* g, fd_reverse* r, void* stream) {
     const RecPlane* inj = row && r->rec_map ? &rp : nullptr;
     if (e != hipSuccess) break;
     if (!pending && i > 0) {
-      e = forward_update(geo, c, r->b_nn, r->b_n1, r->b_nn, r->vdt2, ex, ey, ez, nullptr, s, inj);
+      e = forward_update(geo, c, r->b_nn, r->b_n1, r->b_nn, r->vdt2, ex, ey, ez, nullptr, s, inj,
+                         kBrickPoints);
       pending = r->keep[i];
     } else {
       e = launch_acc(geo, c, r->b_nn, r->b_n1, r->b_nn, r->vdt2, ex, ey, ez, inj, r->keep[i],
@@ -1065,7 +1072,8 @@ static int adjoint_scaled(const fd_grid* g, const float* b_nn, const float* b_n1
   }
   // the forward update run backward in time: b_out = D (2 b_n1 - E b_nn + Q L b_n1),
   // with inj the scaled residual row added at the receivers in the same launch
-  return check_hip(forward_update(geo, c, b_nn, b_n1, b_out, vdt2, ex, ey, ez, nullptr, s, inj),
+  return check_hip(forward_update(geo, c, b_nn, b_n1, b_out, vdt2, ex, ey, ez, nullptr, s, inj,
+                                  kBrickPointsOnce),
                    "fd_adjoint_step_scaled launch");
 }
 

@@ -1,7 +1,7 @@
 // fd_brick.hip -- the forward update and the gradient pass of grids that the caches
 // hold (gfx950).
 //
-// A grid of up to about 12 million points has its four arrays (16 bytes per point) in
+// A grid of up to about 14 million points has its four arrays (16 bytes per point) in
 // the L2 and last-level caches between steps, which stream them at 7-8 TB/s, and its
 // step is over in 4-35 us: too short for a z march, whose blocks spend a few
 // microseconds filling a nine-plane register queue and then wait one memory round trip
@@ -14,6 +14,13 @@
 //     and y neighbours.  Centre planes and halos are loaded first, so that the x and y
 //     terms are computed while the z planes and the pointwise operands arrive;
 //   * about 35 bytes per point pass L1 (KZ = 2), most of them hits in L2.
+// Order of the bricks: an XCD takes a run of consecutive ones, whose u planes overlap by 8
+// of 10 planes and 8 of 24 rows and are to be found in its 4 MB of L2.  With x, y, z
+// order a layer of two planes puts 16 planes (10 of u, 3 x 2 others) between a plane's
+// uses, more than L2 holds from about 50000 points per plane on, so larger planes are
+// taken as bands of rows, each swept through z before the next (338 x 226 x 146 44.2 us
+// per step -> 31.6, 512 x 128 x 128 27.5 -> 22.5, 224^3 31.3 -> 30.4).
+//
 // The arithmetic is that of the marching kernels, term for term and in the same order
 // (centre, x pairs, y pairs, z pairs; the damped form only where eta != 0; the source,
 // residual and receiver epilogues), so every kernel gives the same bits.
@@ -29,9 +36,9 @@
 // Measured (us per step in the native loop, sponge 16, before / after; before: one
 // thread per point up to 160^3, 64 x 32 marching tiles at 192^3, 16-byte marching lanes
 // above): 80^3 5.83 / 4.48, 96^3 6.72 / 5.36, 128^3 9.83 / 7.97, 141 x 119 x 133 15.5 /
-// 9.6, 160^3 19.5 / 13.2, 192^3 26.2 / 20.1, 336 x 150 x 174 31.3 / 25.5, 224^3 37.7 /
-// 30.9 (5.8 TB/s of the 16 bytes per point); 256^3 (268 MB, past the last-level cache)
-// would be 48.7 / 57.1.  A launch of an empty kernel in the same loop takes 2.4 us.
+// 9.6, 160^3 19.5 / 13.2, 192^3 26.2 / 20.1, 336 x 150 x 174 31.3 / 24.7, 224^3 37.7 /
+// 30.4 (5.9 TB/s of the 16 bytes per point), 240^3 44.5 / 40.1; 256^3 (268 MB, past the
+// last-level cache) would be 49.5 / 59.6.  A launch of an empty kernel in the same loop takes 2.4 us.
 // The exchange form (all twelve faces): 96^3 9.80 / 7.35, 128^3 14.3 / 9.45, 160^3 25.5
 // / 16.0, 224^3 47.0 / 37.8, 256^3 54.8 / 67.9.
 //
@@ -70,7 +77,11 @@ struct BrickArgs {
   const float* ey;
   const float* ez;
   int tiles_x, tiles_y;
-  unsigned mx, my;  // ceil(2^31 / tiles_x), ceil(2^31 / tiles_y): division by them
+  // order of the bricks: x fastest, then the y rows of a band (band rows of bricks), then
+  // z, then the bands; span: rows of bricks in a band (band x layers of z); mx, mspan,
+  // mband, mlast: ceil(2^31 / d) of tiles_x, span, band and the last band's rows
+  int band, span;
+  unsigned mx, mspan, mband, mlast;
   int si, sj, sk;   // source point (si < 0: none)
   float sw;
   // receivers on plane rk (rk < 0: none): rmap[j * nx + i] is the receiver index of
@@ -406,9 +417,13 @@ __device__ __forceinline__ void brick_block(const BrickArgs& p, const BrickFaces
 __device__ __forceinline__ void brick_tile(const BrickArgs& p, unsigned logical, int* bx, int* by,
                                            int* bz) {
   const unsigned rest = (unsigned)(((uint64_t)logical * p.mx) >> 31);
-  const unsigned z = (unsigned)(((uint64_t)rest * p.my) >> 31);
+  const unsigned band = (unsigned)(((uint64_t)rest * p.mspan) >> 31);
+  const unsigned in = rest - band * (unsigned)p.span;
+  const int left = p.tiles_y - (int)band * p.band;
+  const unsigned rows = (unsigned)min(p.band, left);
+  const unsigned z = (unsigned)(((uint64_t)in * (left < p.band ? p.mlast : p.mband)) >> 31);
   *bx = (int)(logical - rest * (unsigned)p.tiles_x);
-  *by = (int)(rest - z * (unsigned)p.tiles_y);
+  *by = (int)(band * (unsigned)p.band + in - z * rows);
   *bz = (int)z;
 }
 
@@ -453,6 +468,7 @@ __global__ void __launch_bounds__(8 * TROWS, brick_waves(KZ, B_FWD))
 constexpr long long kOnePlanePoints = 1LL << 20;
 
 int brick_planes(long long points) { return points <= kOnePlanePoints ? 1 : 2; }
+int brick_planes(const Geo& g) { return brick_planes((long long)g.nx * g.ny * g.nz); }
 
 // 16 lanes (64 points) where 64-wide bricks cover at most a tenth more than 32-wide
 // ones (the figures are at the top of this file)
@@ -463,9 +479,25 @@ int brick_lanes(const Geo& g) {
 
 unsigned magic31(int d) { return (unsigned)(((1ull << 31) + d - 1) / d); }
 
+// Rows of bricks per band of the order (see the top) for planes of rows x width points
+// (the bricks' extent): equal bands of about kBandPoints, of any size for planes of at
+// most kWholePoints.  us per step, whole planes / bands of 2, 4, 6 or 8 rows: 338 x 226 x
+// 146 44.2 / 32.5, 31.9, 31.7, -; 512 x 128 x 128 27.5 / 22.5, 22.7, 23.5, -; 256 x 256 x
+// 200 42.4 / 36.9, 35.7, 36.1, 37.1; 512 x 200 x 136 62.2 / 37.5, 37.2, 40.8, 45.3; 192^3
+// 20.4 / 20.9, 20.3, 20.1, -; 96 x 300 x 300 (29k points a plane) 24.6 / 26.8, 25.8, 25.5, -.
+constexpr int kBandPoints = 24576, kWholePoints = 32768;
+
+int brick_band(int width, int rows) {
+  const int row = TROWS * width;
+  if ((long long)rows * row <= kWholePoints) return rows;
+  const int most = std::max(1, (kBandPoints + row / 2) / row);
+  const int bands = (rows + most - 1) / most;
+  return (rows + bands - 1) / bands;
+}
+
 BrickArgs brick_args(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
                      const float* q, const float* ex, const float* ey, const float* ez,
-                     const fd_source* src, const RecPlane* rp, int lanes) {
+                     const fd_source* src, const RecPlane* rp, int lanes, int kz) {
   BrickArgs p{};
   p.g = g;
   p.c = c;
@@ -478,8 +510,13 @@ BrickArgs brick_args(const Geo& g, const Coef& c, const float* up, const float* 
   p.ez = ez;
   p.tiles_x = (g.nx + 4 * lanes - 1) / (4 * lanes);
   p.tiles_y = (g.ny + TROWS - 1) / TROWS;
+  p.band = brick_band(p.tiles_x * 4 * lanes, p.tiles_y);
+  p.span = p.band * ((g.nz + kz - 1) / kz);
   p.mx = magic31(p.tiles_x);
-  p.my = magic31(p.tiles_y);
+  p.mspan = magic31(p.span);
+  p.mband = magic31(p.band);
+  const int last = p.tiles_y % p.band;
+  p.mlast = magic31(last ? last : p.band);
   p.si = p.sj = p.sk = -1;
   if (src) {
     p.si = src->i;
@@ -498,7 +535,7 @@ BrickArgs brick_args(const Geo& g, const Coef& c, const float* up, const float* 
 
 template <bool SPONGE, bool XCH, BrickMode MODE, bool RADD>
 hipError_t launch_bricks(const BrickArgs& p, const BrickFaces& fc, int lanes, hipStream_t s) {
-  const int kz = brick_planes((long long)p.g.nx * p.g.ny * p.g.nz);
+  const int kz = brick_planes(p.g);
   const long long nb = (long long)p.tiles_x * p.tiles_y * ((p.g.nz + kz - 1) / kz);
   if (nb <= 0 || nb > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)nb), block((unsigned)(lanes * TROWS));
@@ -516,29 +553,35 @@ bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15u) == 0; }
 
 }  // namespace
 
-bool brick_grid(const Geo& g) {
+bool brick_grid(const Geo& g, long long most) {
   if (tile_override() != 0) return false;
   if (g.sy % 4 || g.sz % 4 || g.org % 4) return false;
   const long long points = (long long)g.nx * g.ny * g.nz;
-  if (points > kBrickPoints) return false;
+  if (points > most) return false;
   // bricks that cover more than twice the grid (extents far below 32 x 16) waste what
   // the other kernels' shapes do not
   const long long tx = (g.nx + 31) / 32, ty = (g.ny + TROWS - 1) / TROWS;
   if (tx * 32 * ty * TROWS > 2LL * g.nx * g.ny) return false;
-  // the tile division is exact while blocks x divisor stays below 2^31
-  return tx * ty * g.nz * std::max(tx, ty) < (1LL << 31);
+  // the divisions of brick_tile are exact while dividend x divisor stays below 2^31
+  // (blocks by tiles_x, rows of bricks by a band's)
+  const long long kz = brick_planes(g), rows = ty * ((g.nz + kz - 1) / kz);
+  return tx * rows * tx < (1LL << 31) && rows * rows < (1LL << 31);
 }
 
-bool brick_takes(const Geo& g, const float* const arrays[4], const float* const* in,
-                 float* const* out) {
-  if (!brick_grid(g) || (long long)g.nx * g.ny * g.nz <= kBrickLeastPoints) return false;
+bool brick_step(const Geo& g, bool faces, long long most) {
+  const long long lanes = (long long)((g.nx + 63) / 64 * 64) * g.ny * g.nz;
+  if (lanes <= (faces ? kBrickLeastFaces : kBrickLeast)) return false;
+  if (faces && (g.nx % 4 || g.ny < 4 || g.nz < 4)) return false;
+  return brick_grid(g, most);
+}
+
+bool brick_takes(const Geo& g, const float* const arrays[4], long long most,
+                 const float* const* in, float* const* out) {
+  if (!brick_step(g, in != nullptr, most)) return false;
   for (int i = 0; i < 4; ++i)
     if (!arrays[i] || !aligned16(arrays[i])) return false;
-  if (in) {
-    if (g.nx % 4 || g.ny < 4 || g.nz < 4) return false;
-    for (int f = 0; f < 6; ++f)
-      if (!in[f] || !out[f] || !aligned16(in[f]) || !aligned16(out[f])) return false;
-  }
+  for (int f = 0; in && f < 6; ++f)
+    if (!in[f] || !out[f] || !aligned16(in[f]) || !aligned16(out[f])) return false;
   return true;
 }
 
@@ -547,7 +590,7 @@ hipError_t launch_brick(const Geo& g, const Coef& c, const float* up, const floa
                         const fd_source* src, const RecPlane* rp, hipStream_t s,
                         const float* const* in, float* const* out) {
   const int lanes = brick_lanes(g);
-  const BrickArgs p = brick_args(g, c, up, u, un, q, ex, ey, ez, src, rp, lanes);
+  const BrickArgs p = brick_args(g, c, up, u, un, q, ex, ey, ez, src, rp, lanes, brick_planes(g));
   const bool radd = rp && rp->map && rp->add;
   BrickFaces fc{};
   if (in) {
@@ -570,7 +613,7 @@ hipError_t launch_grad_brick(const Geo& g, const Coef& c, const float* u, const 
                              float* gq, const float* ex, const float* ey, const float* ez,
                              const fd_source* src, hipStream_t s) {
   const int lanes = brick_lanes(g);
-  const BrickArgs p = brick_args(g, c, an1, u, gq, gq, ex, ey, ez, src, nullptr, lanes);
+  const BrickArgs p = brick_args(g, c, an1, u, gq, gq, ex, ey, ez, src, nullptr, lanes, brick_planes(g));
   return ex ? launch_bricks<true, false, B_GRAD, false>(p, BrickFaces{}, lanes, s)
             : launch_bricks<false, false, B_GRAD, false>(p, BrickFaces{}, lanes, s);
 }
@@ -580,7 +623,7 @@ hipError_t launch_keep_brick(const Geo& g, const Coef& c, const float* up, const
                              const float* ez, const fd_source* src, const RecPlane* rp,
                              float* keep, hipStream_t s) {
   const int lanes = brick_lanes(g);
-  BrickArgs p = brick_args(g, c, up, u, un, q, ex, ey, ez, src, rp, lanes);
+  BrickArgs p = brick_args(g, c, up, u, un, q, ex, ey, ez, src, rp, lanes, brick_planes(g));
   p.keep = keep;
   return ex ? launch_bricks<true, false, B_KEEP, false>(p, BrickFaces{}, lanes, s)
             : launch_bricks<false, false, B_KEEP, false>(p, BrickFaces{}, lanes, s);
@@ -591,7 +634,7 @@ hipError_t launch_acc_brick(const Geo& g, const Coef& c, const float* up, const 
                             const RecPlane* rp, const float* s1, const float* s2, float* g_acc,
                             hipStream_t s) {
   const int lanes = brick_lanes(g);
-  BrickArgs p = brick_args(g, c, up, u, un, q, ex, ey, ez, nullptr, rp, lanes);
+  BrickArgs p = brick_args(g, c, up, u, un, q, ex, ey, ez, nullptr, rp, lanes, brick_planes(g));
   p.s1 = s1;
   p.s2 = s2;
   p.g_acc = g_acc;
@@ -610,7 +653,7 @@ hipError_t launch_brick_multi(const WideStep* steps, int n, hipStream_t s) {
   for (int i = 0; i < n; ++i) {
     const WideStep& w = steps[i];
     A.start[i] = (int)nb;
-    A.grid[i] = brick_args(w.g, w.c, w.up, w.u, w.un, w.q, w.ex, w.ey, w.ez, &w.src, &w.rec, 8);
+    A.grid[i] = brick_args(w.g, w.c, w.up, w.u, w.un, w.q, w.ex, w.ey, w.ez, &w.src, &w.rec, 8, kz);
     nb += (long long)A.grid[i].tiles_x * A.grid[i].tiles_y * ((w.g.nz + kz - 1) / kz);
     if (nb > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   }

@@ -165,21 +165,42 @@ bool wide_takes_step(const Geo& g, const float* const arrays[4]);
 hipError_t launch_grad_wide(const Geo& g, const Coef& c, const float* u, const float* an1,
                             float* gq, const float* ex, const float* ey, const float* ez,
                             const fd_source* src, hipStream_t s);
-// Grids that the caches hold, stepped as bricks (fd_brick.hip; same bits): more than
-// kBrickLeastPoints interior points (below that one thread per point finishes first: 64^3
-// 3.50 us against 3.47, with the faces exchanged 4.93 against 5.22) and at most
-// kBrickPoints, 200 MB of the 16 bytes per point that a step moves (224^3, 11.2M points:
-// 30.9 us against 37.7 of the marching kernel; 256 x 256 x 200, 13.1M: 43.9 against 41.3).
-constexpr long long kBrickLeastPoints = 1LL << 18;
-constexpr long long kBrickPoints = 12500000;
-// Whether bricks can step g at all: tile mode 0, at most kBrickPoints points, strides
+// Grids that the caches hold, stepped as bricks (fd_brick.hip; same bits).
+//
+// From how many points: those where one thread per point does not finish first, in
+// points of rows rounded up to whole waves (64 points; a row of 68 costs that kernel
+// two).  64^3 x 1.02: 2.69 us a step against 3.23 as bricks, 64 x 96 x 64 3.08 / 3.41,
+// 128 x 64 x 64 3.63 / 3.57, 68^3 (592k) 3.88 / 3.32; with the faces exchanged 64 x 96 x
+// 64 4.68 / 4.63 (arrays not in cache: 5.85 / 6.85), 128 x 64 x 64 5.49 / 4.77 (6.78 /
+// 7.26), 68^3 6.08 / 4.57 (7.66 / 7.23).
+constexpr long long kBrickLeast = 450000;
+constexpr long long kBrickLeastFaces = 550000;
+// Up to how many points.  Updates of a run, whose arrays the caches keep from step to
+// step: 232 MB of the 16 bytes per point (240^3, 13.8M points: 40.1 us against 44.5 of
+// the marching kernel; 448 x 160 x 200, 14.3M: 41.7 / 47.2; 256^3: 59.6 / 49.5).
+constexpr long long kBrickPoints = 14500000;
+// Passes that move more arrays (kept states, gradients, faces) and mixes of several
+// shots: a gradient with kept states at 11.5M points 93 us per step against 115, at
+// 13.1M 117 / 113.5, at 13.8M 131 / 122; 256 x 256 x 200 with faces 44.9 / 45.4.
+constexpr long long kBrickPointsMore = 12500000;
+// A single call, whose arrays may come from memory (a caller stepping several grids in
+// turn): cold, 160^3 20.0 us against 28.0 of the kernel it replaces, 192 x 192 x 128
+// 21.5 / 21.6, 192^3 29.3 / 28.3, 338 x 226 x 146 49.5 / 45.2.  (With faces in the
+// launch: 336 x 152 x 174 46.0 against 48.0, 224^3 52.2 / 56.3, 192^3 35.0 / 34.9, so
+// kBrickPointsMore, except where rows fill the 128-wide tiles of the kernel it replaces:
+// 512 x 128 x 128 38.9 / 36.0.)
+constexpr long long kBrickPointsOnce = 1LL << 22;
+// Whether bricks can step g at all: tile mode 0, at most `most` points, strides
 // and origin multiples of 4 floats, extents that fill the bricks.
-bool brick_grid(const Geo& g);
-// Whether a forward step over g with these arrays (u_prev, u, u_next, vdt2) takes the
+bool brick_grid(const Geo& g, long long most = kBrickPointsMore);
+// The same for an update, with all twelve faces in the launch if so, and enough points
+// to pay.
+bool brick_step(const Geo& g, bool faces, long long most);
+// Whether that step with these arrays (u_prev, u, u_next, vdt2) takes the
 // brick kernel; with in and out (six receive and six send buffers) in the exchange
 // form: all twelve given, 16-byte aligned, nx a multiple of 4.
-bool brick_takes(const Geo& g, const float* const arrays[4], const float* const* in = nullptr,
-                 float* const* out = nullptr);
+bool brick_takes(const Geo& g, const float* const arrays[4], long long most,
+                 const float* const* in = nullptr, float* const* out = nullptr);
 // launch_step_point by the brick kernel, where brick_takes.
 hipError_t launch_brick(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
                         const float* q, const float* ex, const float* ey, const float* ez,

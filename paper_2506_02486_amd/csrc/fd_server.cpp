@@ -464,7 +464,7 @@ hipError_t upload_tables(Server* S) {
   // several grids that the caches hold together are stepped as bricks instead,
   // kBrickMulti of them a launch
   S->bricks.clear();
-  bool all_bricks = points_in_use(S) <= kBrickPoints;
+  bool all_bricks = points_in_use(S) <= kBrickPointsMore;
   for (Shot* s : S->slots)
     if (s) {
       S->bricks.push_back(s);
@@ -489,7 +489,7 @@ hipError_t upload_tables(Server* S) {
     if (const Shot* s = S->direct[f])  // as fd_forward_run samples a lone grid
       S->direct_rows[f] = s->plane_k >= 0 &&
                           (f == 1 || point_kernel_pays(s->geo) || receiver_plane_pays(s->geo) ||
-                           brick_grid(s->geo));
+                           brick_step(s->geo, false, kBrickPointsMore));
   }
   for (const Shot* s : S->slots)
     if (s && S->bricks.empty() && s != S->direct[s->in_wide ? 1 : 0] && !(s->in_wide && !S->multi.empty())) {
@@ -576,7 +576,7 @@ hipError_t step_direct(Server* S, Shot* s, bool rows) {
   const float* u = arr[n % 3];
   float* un = arr[(n + 1) % 3];
   const float* const arrs[4] = {up, u, un, q};
-  if (brick_takes(s->geo, arrs))
+  if (brick_takes(s->geo, arrs, kBrickPointsMore))
     return launch_brick(s->geo, s->coef, up, u, un, q, ex, ey, ez, &src, rows ? &rp : nullptr,
                         S->cs);
   if (s->in_wide)

@@ -1,4 +1,4 @@
-"""The brick kernel (fd_brick.hip), which steps grids of 2^18 to 12.5M points: the same
+"""The brick kernel (fd_brick.hip), which steps grids of 0.45M to 14.5M points: the same
 bits as the other kernels, at the edges of its bricks, and the rule that chooses it."""
 import numpy as np
 import pytest
@@ -11,12 +11,17 @@ api = pytest.importorskip("paper_2506_02486_amd.api")
 
 # one and two planes per brick (up to 2^20 points, above), 8 and 16 lanes; rows whose
 # last float4 holds 1, 2, 3 or 4 interior points; whole and ragged bricks on every axis
-SHAPES = [(70, 66, 61), (65, 64, 64), (64, 80, 53), (99, 47, 71), (131, 101, 83),
-          (128, 96, 90), (190, 83, 77), (96, 113, 97), (132, 100, 81)]
+SHAPES = [(70, 66, 61), (65, 64, 64), (64, 112, 80), (99, 53, 71), (131, 101, 83),
+          (128, 96, 90), (190, 83, 77), (96, 113, 97), (132, 100, 81),
+          # planes taken in bands: one and two planes per brick, equal bands and a
+          # smaller last one; single calls by another kernel (more than 2^22 points)
+          (196, 186, 20), (200, 200, 27), (512, 70, 33), (340, 228, 56)]
 
 
 @pytest.mark.parametrize("shape,faces,want", [
-    ((64, 64, 64), False, False), ((64, 64, 65), False, True), ((224, 224, 224), True, True),
+    ((64, 64, 64), False, False), ((64, 80, 80), False, False), ((64, 128, 64), False, True),
+    ((64, 128, 64), True, False), ((65, 64, 64), False, True), ((224, 224, 224), True, True),
+    ((240, 240, 240), False, True), ((240, 240, 240), True, False),
     ((225, 224, 224), True, False), ((225, 224, 224), False, True),
     ((256, 256, 256), False, False), ((512, 512, 512), True, False),
     ((4, 300, 300), False, False), ((300, 4, 300), False, False), ((640, 640, 2), True, False)])
