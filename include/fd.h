@@ -670,6 +670,13 @@ int fd_server_destroy(void* srv);
 int fd_block_gemm_f64(int64_t m, int64_t n, int64_t k, const double* a, int64_t lda,
                       const double* b, int64_t ldb, double* c, int64_t ldc, int32_t accumulate,
                       void* stream);
+/* The P local steps of rank `rank` (taken mod P) with every B stripe resident: A and C
+ * are its Ns x N stripes, B is N x N, Ns = N / P (P must divide N), and
+ *     C += A[:, q Ns : (q+1) Ns] B[q Ns : (q+1) Ns, :]   for q = rank, rank+1, ... mod P,
+ * product after product (the bits of P calls of fd_block_gemm_f64 with accumulate), in
+ * one launch where that is faster.  Errors as there, for any of the products. */
+int fd_cannon_rank_f64(int64_t n, int32_t parts, int32_t rank, const double* a, int64_t lda,
+                       const double* b, int64_t ldb, double* c, int64_t ldc, void* stream);
 
 #ifdef __cplusplus
 }

@@ -93,6 +93,8 @@ SIGNATURES = {
     "fd_prepare_vdt2": (C.c_int, [_G, _P, _P, _f64, _P]),
     "fd_block_gemm_f64": (C.c_int, [C.c_int64, C.c_int64, C.c_int64, _P, C.c_int64, _P,
                                     C.c_int64, _P, C.c_int64, _i32, _P]),
+    "fd_cannon_rank_f64": (C.c_int, [C.c_int64, _i32, _i32, _P, C.c_int64, _P, C.c_int64, _P,
+                                     C.c_int64, _P]),
     "fd_prepare_vdt2_m": (C.c_int, [_G, _P, _P, _f64, _P]),
     "fd_sponge_eta_max": (_f64, [_f64, _f64, _f64, _i32, _f64]),
     "fd_sponge_profile": (C.c_int, [_P, _i32, _i32, _f64]),

@@ -815,6 +815,11 @@ def cannon_rank(A_r: torch.Tensor, B: torch.Tensor, C_r: torch.Tensor, rank: int
     if B.shape != (N, N) or N % P or A_r.shape != (N // P, N) or C_r.shape != (N // P, N):
         raise ValueError("cannon_rank: stripes of N/P x N and an N x N B are needed")
     ns = N // P
+    if ns >= 32:  # all of them in one call (below, blocks may be single columns of A_r)
+        check(lib().fd_cannon_rank_f64(N, P, rank % P, A_r.data_ptr(), _ld(A_r, "a"), B.data_ptr(),
+                                       _ld(B, "b"), C_r.data_ptr(), _ld(C_r, "c"),
+                                       _stream(stream)), "fd_cannon_rank_f64")
+        return C_r
     for q in cannon_order(rank, P):
         block_gemm(A_r[:, q * ns:(q + 1) * ns], B[q * ns:(q + 1) * ns, :], C_r, True, stream)
     return C_r

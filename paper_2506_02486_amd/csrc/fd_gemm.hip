@@ -20,9 +20,11 @@
 //     one before, and the last k-step's MFMAs run after the barrier, while the first
 //     fragments of the next stage arrive;
 //   * LDS accesses and loads are issued one MFMA at a time (sched_group_barrier).
-// 3780 x 30240 x 3780: 65.3 -> 67.4-68.1 TFLOP/s; 8192^3: 68.2 -> 70.3-71.0 (vendor BLAS 72.1 on
-// the same box).  Writing a stage earlier alone gave nothing (64.4), with the double
-// fragments 67.4.
+//   * the loop takes two stages a turn, so that the LDS buffer is known when compiling
+//     and no address is computed between the barrier and the reads behind it.
+// 3780 x 30240 x 3780: 65.3 -> 69.1 TFLOP/s (67.4 with the buffer chosen at run time);
+// 8192^3: 68.2 -> 70.3-71.0 before that (vendor BLAS 72.1 on the same box).  Writing a
+// stage earlier alone gave nothing (64.4), with the double fragments 67.4.
 //
 // Smaller products (gemm_pair_kernel) leave most CUs idle with 256 x 128 tiles (512 x
 // 4096 x 512, one of Cannon's products at N = 4096 and P = 8: 64 tiles on 256 CUs), so
@@ -38,6 +40,17 @@
 // 18.3, 256 x 2048 x 256 72 / 8.8, 52 x 260 x 52 26 / 7.7 (the launch rate of the loop
 // that timed it).
 //
+// The products of one rank (fd_cannon_rank_f64) in one launch (PARTS), where the tiles are 64
+// x 64 or 32 x 64: a block takes its tile through all of them, the loads of the next
+// product's first stage issued during the last stages of the one before, and adds each
+// to the C it holds in registers, so the bits are those of the separate products.
+// Separately, each of them starts with an empty pipeline, ends with a last wave of tiles
+// and reads and writes C, and small ones are over before the next is launched (us, P
+// launches / one): 8 x 32 x 256 x 32 91 / 9.2, 8 x 135 x 1080 x 135 91 / 32, 4 x 446 x
+// 1784 x 446 84.8 / 75.0, 8 x 512 x 4096 x 512 325 / 278, 5 x 927 x 4635 x 927 795 / 753.
+// The larger tiles have no registers for the sum beside the accumulators (128 x 128: 617
+// against 606 separately at 6 x 736 x 4416 x 736).
+//
 // Operands of any shape and leading dimension: K is split into a first stage of 1 to a
 // whole stage's columns, whose loads past K read 0, and whole stages, whose loads need no
 // bounds arithmetic (an offset per thread from the tile's base plus the stage's offset);
@@ -48,6 +61,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "fd.h"
 #include "fd_internal.h"
@@ -92,7 +106,41 @@ struct GemmArgs {
   int64_t ldc;
   int tiles_m;
   int accumulate;
+  // PARTS: k is one part of K; part q is columns q k .. of A and rows q k .. of B, and
+  // the products of all of them, from part `first` on and around, are added to C one
+  // after the other (k >= 32, accumulate)
+  int parts, first;
 };
+
+// The stages of all parts in order: the addresses of the one to load next, kept ready so
+// that its loads wait for no arithmetic.  They are consecutive columns of A and rows of B
+// but where the last part is followed by part 0; past the last stage they stay.
+struct Stages {
+  const double *a, *b;  // of the next stage
+  int lim;              // its columns that count: kt in a part's first stage, else bk
+  int kt, bk, per;      // per: stages of a part
+  int s, part, left;    // stage within the part, part, stages after this one
+  __device__ __forceinline__ void step(const GemmArgs& g) {
+    if (left == 0) return;
+    --left;
+    a += lim;
+    b += lim * g.ldb;
+    const bool next = ++s == per;
+    s = next ? 0 : s;
+    part += next ? 1 : 0;
+    if (part == g.parts) {
+      part = 0;
+      a -= g.parts * g.k;
+      b -= g.parts * g.k * g.ldb;
+    }
+    lim = next ? kt : bk;
+  }
+};
+
+// Which of the two LDS buffers a stage is in, known when compiling (loops take two stages a
+// turn), so that no address is computed between the barrier and the reads behind it.
+template <int B>
+using Parity = std::integral_constant<int, B>;
 
 // Blocks b, b+8, b+16, ... run on one XCD; give each XCD a contiguous run of
 // logical tiles (row tiles fastest: the tiles of one B panel).
@@ -206,8 +254,8 @@ __global__ void __launch_bounds__(GT, WAVES_PER_SIMD) gemm_f64_kernel(GemmArgs g
   constexpr int NQ = BK / 4;
   static_assert(NQ % 2 == 0, "the fragment sets alternate over a stage");
   frags(0, 0, 0);
-  for (int64_t s = 0; s < stages; ++s) {
-    const int buf = (int)(s & 1);
+  auto stage = [&](auto parity, int64_t s) {
+    constexpr int buf = decltype(parity)::value;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
       __builtin_amdgcn_sched_barrier(0);
@@ -243,30 +291,37 @@ __global__ void __launch_bounds__(GT, WAVES_PER_SIMD) gemm_f64_kernel(GemmArgs g
         }
       }
     }
+  };
+  int64_t s = 0;
+  for (; s + 1 < stages; s += 2) {
+    stage(Parity<0>(), s);
+    stage(Parity<1>(), s + 1);
   }
+  if (s < stages) stage(Parity<0>(), s);
 
   // accumulator element v of lane l holds row l / 16 + 4 v, column l % 16 of its
   // 16 x 16 tile (the lane layout of v_mfma_f64_16x16x4f64, checked with one-hot
   // operands on the device)
+  int tt = t;
+  asm volatile("" : "+v"(tt));  // keeps these addresses out of the loop's registers
+  const int r0 = (tt >> 6) / WAVES_N * WTM + ((tt & 63) >> 4);
+  const int c0 = (tt >> 6) % WAVES_N * WTN + (tt & 15);
+  double* const ct = g.c + (m0 + r0) * g.ldc + n0 + c0;
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int64_t col = n0 + wn + 16 * j + fr;
+    for (int v = 0; v < 4; ++v) {
+      double* const p = ct + (16 * i + 4 * v) * g.ldc;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t row = m0 + wm + 16 * i + fk + 4 * v;
-        if (row < g.m && col < g.n) {
-          double* p = g.c + row * g.ldc + col;
-          *p = g.accumulate ? *p + acc[i][j][v] : acc[i][j][v];
-        }
-      }
+      for (int j = 0; j < FN; ++j)
+        if (r0 + 16 * i + 4 * v <= mr && c0 + 16 * j <= nr)
+          p[16 * j] = g.accumulate ? p[16 * j] + acc[i][j][v] : acc[i][j][v];
     }
 }
 
 // Tiles of PM x PN of waves of VM x VN, stages of PK columns; at most 16 waves per CU
 // (four per SIMD) in the register budget.
-template <int PM, int PN, int VM, int VN, int PK>
+template <int PM, int PN, int VM, int VN, int PK, bool PARTS>
 __global__ void __launch_bounds__(64 * (PM / VM) * (PN / VN), WAVES_PER_SIMD)
     gemm_pair_kernel(GemmArgs g) {
   constexpr int WN = PN / VN;
@@ -288,8 +343,16 @@ __global__ void __launch_bounds__(64 * (PM / VM) * (PN / VN), WAVES_PER_SIMD)
   const int wm = (w / WN) * VM, wn = (w % WN) * VN;
   const int64_t stages = (g.k + PK - 1) / PK;  // k >= 1
   const int64_t kt = g.k - (stages - 1) * PK;
+  const int64_t all = PARTS ? stages * g.parts : stages;
   const double* At = g.a + m0 * g.lda;
   const double* Bt = g.b + n0;
+  if (PARTS) {
+    At += g.first * g.k;
+    Bt += g.first * g.k * g.ldb;
+  }
+  Stages st{At, Bt, (int)kt, (int)kt, PK, (int)stages, 0, g.first, (int)stages * g.parts - 1};
+  if (PARTS) st.step(g);  // (the first is loaded below)
+  int lim = PK;  // columns of the stage in ra and rb that count
   const int mr = (int)std::min<int64_t>(g.m - m0, PM) - 1;
   const int nr = (int)std::min<int64_t>(g.n - n0, PN) - 1;
   // thread's pair i of A: row e / KP, pair e % KP; of B: pair row e / PN, column e % PN
@@ -310,8 +373,9 @@ __global__ void __launch_bounds__(64 * (PM / VM) * (PN / VN), WAVES_PER_SIMD)
   d2 ra[NA], rb[NB];
   auto load_stage = [&](int64_t s) {  // whole stage 1 <= s < stages
     const int64_t k0 = kt + (s - 1) * PK;
-    const double* Ak = At + k0;
-    const double* Bk = Bt + k0 * g.ldb;
+    const double* Ak = PARTS ? st.a : At + k0;
+    const double* Bk = PARTS ? st.b : Bt + k0 * g.ldb;
+    lim = st.lim;
 #pragma unroll
     for (int i = 0; i < NA; ++i) ra[i] = *reinterpret_cast<const d2u*>(Ak + oa[i]);
 #pragma unroll
@@ -319,6 +383,7 @@ __global__ void __launch_bounds__(64 * (PM / VM) * (PN / VN), WAVES_PER_SIMD)
       rb[i][0] = Bk[ob[i]];
       rb[i][1] = (Bk + g.ldb)[ob[i]];
     }
+    if (PARTS) st.step(g);
   };
   auto store_stage = [&](int buf) {
 #pragma unroll
@@ -367,7 +432,7 @@ __global__ void __launch_bounds__(64 * (PM / VM) * (PN / VN), WAVES_PER_SIMD)
 #pragma unroll
     for (int j = 0; j < FJ; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
   store_stage(0);
-  if (stages > 1) load_stage(1);
+  if (all > 1) load_stage(1);
   __syncthreads();
   // fragments of a pair of k-steps: lane l holds k = 8 p + 2 (l / 16) + {0, 1} of row /
   // column l % 16
@@ -392,8 +457,18 @@ __global__ void __launch_bounds__(64 * (PM / VM) * (PN / VN), WAVES_PER_SIMD)
                                                            acc[i][j], 0, 0, 0);
   };
   frags(0, 0, 0);
-  for (int64_t s = 0; s + 1 < stages; ++s) {
+  int64_t last = stages - 1;  // PARTS: the current part's last stage
+  for (int64_t s = 0; s + 1 < all; ++s) {
     const int buf = (int)(s & 1);
+    if (PARTS && lim < PK) {  // a part's first stage is to be stored: clear its rest
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) ra[i][h] = 2 * ((t + PT * i) % KP) + h < lim ? ra[i][h] : 0.0;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) rb[i][h] = 2 * ((t + PT * i) / PN) + h < lim ? rb[i][h] : 0.0;
+      }
+    }
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
       __builtin_amdgcn_sched_barrier(0);
@@ -411,10 +486,21 @@ __global__ void __launch_bounds__(64 * (PM / VM) * (PN / VN), WAVES_PER_SIMD)
         load_stage(std::min(s + 2, stages - 1));
       }
     }
+    if (PARTS && s == last) {
+      last += stages;
+#pragma unroll
+      for (int i = 0; i < FI; ++i)
+#pragma unroll
+        for (int j = 0; j < FJ; ++j) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) c0[i][j][v] += acc[i][j][v];
+          acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+        }
+    }
   }
 #pragma unroll
   for (int q = 0; q < NP; ++q) {
-    if (q < NP - 1) frags((q + 1) & 1, (int)((stages - 1) & 1), q + 1);
+    if (q < NP - 1) frags((q + 1) & 1, (int)((all - 1) & 1), q + 1);
     mma(q & 1);
   }
 #pragma unroll
@@ -441,16 +527,17 @@ struct TileCost {
 };
 // From 2048 x 8192 x 2048 (every CU has several tiles) and, alone, from products with one
 // tile per CU (1000 x 4000 x 1000, 256 x 2048 x 256) or fewer.
-constexpr TileCost kTiles[4] = {{256, 128, 3.93, 4.15},
+constexpr TileCost kTiles[4] = {{256, 128, 3.86, 3.90},
                                 {128, 128, 2.04, 2.09},
                                 {64, 64, 0.552, 0.69},
                                 {32, 64, 0.302, 0.40}};
 
 // The tile shape of least modelled time: the fullest CU's tiles, one after the other.
-// The model is within 8% of the measured time of every shape on 512 x 4096 x 512, 1285 x
-// 7710 x 1285, 2048 x 8192 x 2048 and 3780 x 30240 x 3780, so its choice is the fastest or
-// as good: 52.7 TFLOP/s (64 x 64; 30.5 with 128 x 128), 57.0 (64 x 64; 50.6), 68.2 (256 x
-// 128; 65.6) and 68.1 (256 x 128; 65.5).
+// The model is within 8% of the measured time of every shape on 512 x 4096 x 512, 972 x 7776
+// x 972, 1285 x 7710 x 1285, 1875 x 7500 x 1875, 2048 x 8192 x 2048 and 3780 x 30240 x
+// 3780, so its choice is the fastest or as good (us with 256 x 128, 128 x 128 and 64 x 64):
+// 132 / 72 / 41, 245 / 263 / 269, 621 / 507 / 450, 907 / 966 / 913, 994 / 1059 / 1127 and
+// 12502 / 13342 / 14570.
 int gemm_tile(int64_t m, int64_t n) {
   int best = 0;
   double cost = -1.0;
@@ -465,6 +552,18 @@ int gemm_tile(int64_t m, int64_t n) {
     }
   }
   return best;
+}
+
+// Tiles up to which all products of a rank go in one launch: 1095 (5 x 927 x 4635 x 927) 753
+// us against 795, 1683 (6 x 1051 x 6306 x 1051) 1536 / 1546, 3100 (5 x 1582 x 7910 x 1582)
+// 3655 / 3498.
+constexpr int64_t kPartsTiles = 2048;
+
+bool one_launch_pays(int64_t m, int64_t n) {
+  const int tile = gemm_tile(m, n);
+  const int64_t tiles = (m + kTiles[tile].m - 1) / kTiles[tile].m *
+                        ((n + kTiles[tile].n - 1) / kTiles[tile].n);
+  return tile >= 2 && tiles <= kPartsTiles;
 }
 
 // Offsets from a tile's base fit 32 bits: at most 256 rows of A or 32 of B.
@@ -489,50 +588,93 @@ bool ranges_overlap(const void* p, int64_t pn, const void* q, int64_t qn) {
 
 using namespace fd;
 
-extern "C" int fd_block_gemm_f64(int64_t m, int64_t n, int64_t k, const double* a, int64_t lda,
-                                 const double* b, int64_t ldb, double* c, int64_t ldc,
-                                 int32_t accumulate, void* stream) {
-  if (m < 0 || n < 0 || k < 0) return fail(FD_EINVAL, "fd_block_gemm_f64: negative extent");
-  if (m == 0 || n == 0) return FD_OK;
-  if (!c) return fail(FD_EINVAL, "fd_block_gemm_f64: c is NULL");
-  if (ldc < n) return fail(FD_EINVAL, "fd_block_gemm_f64: ldc < n");
+namespace {
+
+// The argument checks of one product, in its own name.
+int gemm_checked(int64_t m, int64_t n, int64_t k, const double* a, int64_t lda, const double* b,
+                 int64_t ldb, const double* c, int64_t ldc, const char* who) {
+  if (!c) return fail(FD_EINVAL, "%s: c is NULL", who);
+  if (ldc < n) return fail(FD_EINVAL, "%s: ldc < n", who);
   if (k > 0) {
-    if (!a || !b) return fail(FD_EINVAL, "fd_block_gemm_f64: a or b is NULL");
-    if (lda < k || ldb < n) return fail(FD_EINVAL, "fd_block_gemm_f64: lda < k or ldb < n");
+    if (!a || !b) return fail(FD_EINVAL, "%s: a or b is NULL", who);
+    if (lda < k || ldb < n) return fail(FD_EINVAL, "%s: lda < k or ldb < n", who);
     const int64_t cb = extent_bytes(m, n, ldc);
     if (ranges_overlap(c, cb, a, extent_bytes(m, k, lda)) ||
         ranges_overlap(c, cb, b, extent_bytes(k, n, ldb)))
-      return fail(FD_EINVAL, "fd_block_gemm_f64: c overlaps a or b");
+      return fail(FD_EINVAL, "%s: c overlaps a or b", who);
   }
+  return FD_OK;
+}
+
+// parts of k columns each, from part `first` on (parts == 1: one product)
+int gemm_run(int64_t m, int64_t n, int64_t k, int parts, int first, const double* a, int64_t lda,
+             const double* b, int64_t ldb, double* c, int64_t ldc, int accumulate,
+             hipStream_t s, const char* who) {
   // (k == 0 only clears or keeps C, and large leading dimensions need 64-bit offsets:
   // both by the first kernel)
   const bool fits = gemm_offsets_fit(lda, ldb);
   const int tile = k > 0 && fits ? gemm_tile(m, n) : 0;
   const int64_t tm = (m + kTiles[tile].m - 1) / kTiles[tile].m;
   const int64_t tn = (n + kTiles[tile].n - 1) / kTiles[tile].n;
-  if (tm * tn > 0x7fffffffLL || tm > 0x7fffffffLL)
-    return fail(FD_EINVAL, "fd_block_gemm_f64: too many tiles");
-  GemmArgs g;
-  g.m = m;
-  g.n = n;
-  g.k = k;
-  g.a = a;
-  g.lda = lda;
-  g.b = b;
-  g.ldb = ldb;
-  g.c = c;
-  g.ldc = ldc;
-  g.tiles_m = (int)tm;
-  g.accumulate = accumulate ? 1 : 0;
+  if (tm * tn > 0x7fffffffLL || tm > 0x7fffffffLL) return fail(FD_EINVAL, "%s: too many tiles", who);
+  const GemmArgs g{m, n, k, a, lda, b, ldb, c, ldc, (int)tm, accumulate, parts, first};
   const dim3 grid((unsigned)(tm * tn));
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  switch (tile) {
-    case 1: hipLaunchKernelGGL((gemm_pair_kernel<128, 128, 32, 32, 16>), grid, dim3(1024), 0, s, g); break;
-    case 2: hipLaunchKernelGGL((gemm_pair_kernel<64, 64, 16, 32, 16>), grid, dim3(512), 0, s, g); break;
-    case 3: hipLaunchKernelGGL((gemm_pair_kernel<32, 64, 16, 16, 32>), grid, dim3(512), 0, s, g); break;
-    default:
-      if (fits) hipLaunchKernelGGL(gemm_f64_kernel<unsigned>, grid, dim3(GT), 0, s, g);
-      else hipLaunchKernelGGL(gemm_f64_kernel<int64_t>, grid, dim3(GT), 0, s, g);
+  void (*kernel)(GemmArgs) = fits ? gemm_f64_kernel<unsigned> : gemm_f64_kernel<int64_t>;
+  int threads = GT;
+  if (tile == 1) {
+    kernel = gemm_pair_kernel<128, 128, 32, 32, 16, false>;
+    threads = 1024;
+  } else if (tile == 2) {
+    kernel = parts > 1 ? gemm_pair_kernel<64, 64, 16, 32, 16, true>
+                       : gemm_pair_kernel<64, 64, 16, 32, 16, false>;
+    threads = 512;
+  } else if (tile == 3) {
+    kernel = parts > 1 ? gemm_pair_kernel<32, 64, 16, 16, 32, true>
+                       : gemm_pair_kernel<32, 64, 16, 16, 32, false>;
+    threads = 512;
   }
-  return check_hip(hipGetLastError(), "fd_block_gemm_f64 launch");
+  hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, s, g);
+  return check_hip(hipGetLastError(), who);
+}
+
+}  // namespace
+
+extern "C" int fd_block_gemm_f64(int64_t m, int64_t n, int64_t k, const double* a, int64_t lda,
+                                 const double* b, int64_t ldb, double* c, int64_t ldc,
+                                 int32_t accumulate, void* stream) {
+  if (m < 0 || n < 0 || k < 0) return fail(FD_EINVAL, "fd_block_gemm_f64: negative extent");
+  if (m == 0 || n == 0) return FD_OK;
+  const int rc = gemm_checked(m, n, k, a, lda, b, ldb, c, ldc, "fd_block_gemm_f64");
+  if (rc) return rc;
+  return gemm_run(m, n, k, 1, 0, a, lda, b, ldb, c, ldc, accumulate ? 1 : 0,
+                  reinterpret_cast<hipStream_t>(stream), "fd_block_gemm_f64");
+}
+
+extern "C" int fd_cannon_rank_f64(int64_t n, int32_t parts, int32_t rank, const double* a,
+                                  int64_t lda, const double* b, int64_t ldb, double* c,
+                                  int64_t ldc, void* stream) {
+  const char* who = "fd_cannon_rank_f64";
+  if (n < 0 || parts < 1 || n % parts) return fail(FD_EINVAL, "%s: n is not P stripes", who);
+  const int64_t ns = n / parts;
+  if (ns == 0) return FD_OK;
+  const int first = (int)(((int64_t)rank % parts + parts) % parts);
+  for (int i = 0; i < parts; ++i) {
+    const int q = (first + i) % parts;
+    const int rc = gemm_checked(ns, n, ns, a ? a + q * ns : a, lda, b ? b + q * ns * ldb : b, ldb,
+                                c, ldc, who);
+    if (rc) return rc;
+  }
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  // one launch for all products in 64 x 64 and 32 x 64 tiles, from ns = 32 on (a part's
+  // first stage is read whole) and up to kPartsTiles: with more tiles, blocks in
+  // different parts of K share less of the B panels in L2
+  if (ns >= 32 && gemm_offsets_fit(lda, ldb) && one_launch_pays(ns, n))
+    return gemm_run(ns, n, ns, parts, first, a, lda, b, ldb, c, ldc, 1, s, who);
+  for (int i = 0; i < parts; ++i) {
+    const int q = (first + i) % parts;
+    const int rc = gemm_run(ns, n, ns, 1, 0, a + q * ns, lda, b + q * ns * ldb, ldb, c, ldc, 1, s,
+                            who);
+    if (rc) return rc;
+  }
+  return FD_OK;
 }

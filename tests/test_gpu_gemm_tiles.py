@@ -45,3 +45,21 @@ def test_large_tiles(k):  # 256 x 128
 @pytest.mark.parametrize("ld", [(1 << 23) + 1, (1 << 23) - 1])
 def test_large_leading_dimension(ld):  # 64-bit offsets, and the last 32-bit ones
     _check(3, 70, 37, True, pad=(ld - 37, 5, 2))
+
+
+# several products in one launch (64 x 64 and 32 x 64 tiles; stages of a product that are
+# whole, ragged and, at 32, single) and in several (the larger tiles: 128 x 128 at 4400,
+# 256 x 128 at 6146), in the ring order from any rank
+@pytest.mark.parametrize("N,P,rank", [(64, 2, 1), (99, 3, 0), (160, 5, 3), (185, 5, 4), (96, 4, 2),
+                                      (1026, 6, 5), (4096, 8, 7), (4400, 5, 1), (6146, 2, 1)])
+def test_cannon_launch_gives_the_bits_of_its_products(N, P, rank):
+    ns = N // P
+    g = torch.Generator(device="cuda").manual_seed(N + P)
+    A = torch.randn((ns, N + 3), generator=g, dtype=torch.float64, device="cuda")[:, :N]
+    B = torch.randn((N, N + 1), generator=g, dtype=torch.float64, device="cuda")[:, :N]
+    C = torch.randn((ns, N + 2), generator=g, dtype=torch.float64, device="cuda")
+    want = C.clone()
+    for q in api.cannon_order(rank, P):
+        api.block_gemm(A[:, q * ns:(q + 1) * ns], B[q * ns:(q + 1) * ns, :], want[:, :N], True)
+    api.cannon_rank(A, B, C[:, :N], rank, P)
+    assert torch.equal(C, want)
