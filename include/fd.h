@@ -130,7 +130,7 @@ int fd_set_kchunk(int32_t kchunk);
 /* Performance knob: tile shape of the forward stencil kernels (fd_step,
  * fd_step_fused, fd_step_exchange, fd_forward_run, fd_adjoint_step_scaled):
  * 0 = automatic: grids of more than 0.45 million points (rows rounded up to 64)
- * and, in a run, at most 14.5 million, whose arrays stay in cache between steps, run
+ * and, in a run, at most 14.5 million (15.5 in whole bricks), whose arrays stay in cache between steps, run
  * as bricks (fd_step_bricks tells which): forward updates, fd_step_exchange /
  * fd_forward_run with all twelve face buffers (0.55 to 12.5 million points, nx a
  * multiple of 4; the faces then read and written in that one launch), and gradient
@@ -628,9 +628,8 @@ int shot_poll(void* srv, int64_t shot_id, float* traces_host, size_t cap, int64_
  * default) a shot joins if the interior points of the running shots and its own stay
  * within the fill, 256 x 128 x 32 x 8 = 8,388,608 (each of the 256 CUs one 128 x 32
  * tile of 8 z planes: grids that together leave the device short of work), or, while
- * more shots wait behind it (a backlog), within twice that (one launch of two
- * mid-size grids beats two launches); with max_active_points > 0 if they
- * stay within that many.  A shot always joins when none runs.  FD_EINVAL for a NULL
+ * more shots wait behind it (a backlog), within twice that; with max_active_points > 0
+ * if they stay within that many.  A shot always joins when none runs.  FD_EINVAL for a NULL
  * server or a negative limit.  Thread-safe. */
 int fd_server_set_admission(void* srv, int64_t max_active_points);
 /* Allocator of the shots' blocks in the arena (the paper's global segment carved by

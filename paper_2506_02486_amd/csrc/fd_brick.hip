@@ -562,6 +562,7 @@ bool brick_grid(const Geo& g, long long most) {
   // the other kernels' shapes do not
   const long long tx = (g.nx + 31) / 32, ty = (g.ny + TROWS - 1) / TROWS;
   if (tx * 32 * ty * TROWS > 2LL * g.nx * g.ny) return false;
+  if (tx * 32 * ty * TROWS * g.nz > kBrickCover) return false;
   // the divisions of brick_tile are exact while dividend x divisor stays below 2^31
   // (blocks by tiles_x, rows of bricks by a band's)
   const long long kz = brick_planes(g), rows = ty * ((g.nz + kz - 1) / kz);

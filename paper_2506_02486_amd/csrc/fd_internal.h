@@ -179,6 +179,11 @@ constexpr long long kBrickLeastFaces = 550000;
 // step: 232 MB of the 16 bytes per point (240^3, 13.8M points: 40.1 us against 44.5 of
 // the marching kernel; 448 x 160 x 200, 14.3M: 41.7 / 47.2; 256^3: 59.6 / 49.5).
 constexpr long long kBrickPoints = 14500000;
+// And up to how many points that the bricks cover (32 x 16 of them at a time): 78 x 300 x
+// 480, 14.0M covered, 49.1 us against 55.2, 260 x 230 x 220 (15.2M) 41.7 / 57.7, 48 x 400 x
+// 600 (15.4M) 53.9 / 53.5, 100 x 300 x 400 (15.6M) 51.2 / 48.9, 78 x 348 x 499 (16.9M)
+// 61.9 / 60.9, 36 x 500 x 650 (21.3M) 80.0 / 65.9.
+constexpr long long kBrickCover = 15500000;
 // Passes that move more arrays (kept states, gradients, faces) and mixes of several
 // shots: a gradient with kept states at 11.5M points 93 us per step against 115, at
 // 13.1M 117 / 113.5, at 13.8M 131 / 122; 256 x 256 x 200 with faces 44.9 / 45.4.
@@ -190,7 +195,8 @@ constexpr long long kBrickPointsMore = 12500000;
 // kBrickPointsMore, except where rows fill the 128-wide tiles of the kernel it replaces:
 // 512 x 128 x 128 38.9 / 36.0.)
 constexpr long long kBrickPointsOnce = 1LL << 22;
-// Whether bricks can step g at all: tile mode 0, at most `most` points, strides
+// Whether bricks can step g at all: tile mode 0, at most `most` points and kBrickCover
+// covered, strides
 // and origin multiples of 4 floats, extents that fill the bricks.
 bool brick_grid(const Geo& g, long long most = kBrickPointsMore);
 // The same for an update, with all twelve faces in the launch if so, and enough points

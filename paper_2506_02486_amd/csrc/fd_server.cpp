@@ -94,6 +94,10 @@ constexpr long long kFillPoints = 256LL * 128 * 32 * 8;
 // prices one launch of the running shots and the new one below the two launches apart
 // ran more shots together and gave 0.987x: the model overrates one launch of two large
 // grids.
+// Since mid-size grids run alone as bricks, in cache, they no longer gain from sharing a
+// launch of the 16-byte-lane kernel (two of 8M points: 59 us together, 2 x 23.7 apart):
+// 34.89 shots/s on the 128..384^3 mix with this limit, 35.32 with the 12.5M that are
+// stepped together as bricks.
 constexpr long long kBacklogPoints = 2 * kFillPoints;
 
 size_t align_up(size_t n) { return (n + kAlign - 1) / kAlign * kAlign; }
@@ -489,7 +493,7 @@ hipError_t upload_tables(Server* S) {
     if (const Shot* s = S->direct[f])  // as fd_forward_run samples a lone grid
       S->direct_rows[f] = s->plane_k >= 0 &&
                           (f == 1 || point_kernel_pays(s->geo) || receiver_plane_pays(s->geo) ||
-                           brick_step(s->geo, false, kBrickPointsMore));
+                           brick_step(s->geo, false, kBrickPoints));
   }
   for (const Shot* s : S->slots)
     if (s && S->bricks.empty() && s != S->direct[s->in_wide ? 1 : 0] && !(s->in_wide && !S->multi.empty())) {
@@ -576,7 +580,7 @@ hipError_t step_direct(Server* S, Shot* s, bool rows) {
   const float* u = arr[n % 3];
   float* un = arr[(n + 1) % 3];
   const float* const arrs[4] = {up, u, un, q};
-  if (brick_takes(s->geo, arrs, kBrickPointsMore))
+  if (brick_takes(s->geo, arrs, kBrickPoints))
     return launch_brick(s->geo, s->coef, up, u, un, q, ex, ey, ez, &src, rows ? &rp : nullptr,
                         S->cs);
   if (s->in_wide)

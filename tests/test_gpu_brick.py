@@ -22,6 +22,7 @@ SHAPES = [(70, 66, 61), (65, 64, 64), (64, 112, 80), (99, 53, 71), (131, 101, 83
     ((64, 64, 64), False, False), ((64, 80, 80), False, False), ((64, 128, 64), False, True),
     ((64, 128, 64), True, False), ((65, 64, 64), False, True), ((224, 224, 224), True, True),
     ((240, 240, 240), False, True), ((240, 240, 240), True, False),
+    ((78, 300, 480), False, True), ((100, 300, 400), False, False),
     ((225, 224, 224), True, False), ((225, 224, 224), False, True),
     ((256, 256, 256), False, False), ((512, 512, 512), True, False),
     ((4, 300, 300), False, False), ((300, 4, 300), False, False), ((640, 640, 2), True, False)])
