@@ -28,7 +28,7 @@
 //
 // Smaller products (gemm_pair_kernel) leave most CUs idle with 256 x 128 tiles (512 x
 // 4096 x 512, one of Cannon's products at N = 4096 and P = 8: 64 tiles on 256 CUs), so
-// they take 128 x 128, 64 x 64 or 32 x 64 tiles, whichever the cost model below
+// they take 128 x 128, 64 x 64, 32 x 64 or 32 x 32 tiles, whichever the cost model below
 // (gemm_tile) prices lowest.  Their waves own 32 x 32, 16 x 32 or 16 x 16 pieces, for
 // which fragment reads of single doubles would bound the kernel (58 of LDS's 128 bytes
 // per clock at 64 x 64, as 8-byte reads): K is kept in pairs in LDS (A [m][k], B [k/2][n]
@@ -41,12 +41,12 @@
 // that timed it).
 //
 // The products of one rank (fd_cannon_rank_f64) in one launch (PARTS), where the tiles are 64
-// x 64 or 32 x 64: a block takes its tile through all of them, the loads of the next
+// x 64 or smaller: a block takes its tile through all of them, the loads of the next
 // product's first stage issued during the last stages of the one before, and adds each
 // to the C it holds in registers, so the bits are those of the separate products.
 // Separately, each of them starts with an empty pipeline, ends with a last wave of tiles
 // and reads and writes C, and small ones are over before the next is launched (us, P
-// launches / one): 8 x 32 x 256 x 32 91 / 9.2, 8 x 135 x 1080 x 135 91 / 32, 4 x 446 x
+// launches / one): 8 x 32 x 256 x 32 91 / 9.2, 8 x 135 x 1080 x 135 91 / 24, 4 x 446 x
 // 1784 x 446 84.8 / 75.0, 8 x 512 x 4096 x 512 325 / 278, 5 x 927 x 4635 x 927 795 / 753.
 // The larger tiles have no registers for the sum beside the accumulators (128 x 128: 617
 // against 606 separately at 6 x 736 x 4416 x 736).
@@ -527,21 +527,24 @@ struct TileCost {
 };
 // From 2048 x 8192 x 2048 (every CU has several tiles) and, alone, from products with one
 // tile per CU (1000 x 4000 x 1000, 256 x 2048 x 256) or fewer.
-constexpr TileCost kTiles[4] = {{256, 128, 3.86, 3.90},
+constexpr TileCost kTiles[5] = {{256, 128, 3.86, 3.90},
                                 {128, 128, 2.04, 2.09},
                                 {64, 64, 0.552, 0.69},
-                                {32, 64, 0.302, 0.40}};
+                                {32, 64, 0.302, 0.40},
+                                {32, 32, 0.14, 0.29}};
 
 // The tile shape of least modelled time: the fullest CU's tiles, one after the other.
 // The model is within 8% of the measured time of every shape on 512 x 4096 x 512, 972 x 7776
 // x 972, 1285 x 7710 x 1285, 1875 x 7500 x 1875, 2048 x 8192 x 2048 and 3780 x 30240 x
 // 3780, so its choice is the fastest or as good (us with 256 x 128, 128 x 128 and 64 x 64):
 // 132 / 72 / 41, 245 / 263 / 269, 621 / 507 / 450, 907 / 966 / 913, 994 / 1059 / 1127 and
-// 12502 / 13342 / 14570.
+// 12502 / 13342 / 14570.  Small ones with 64 x 64, 32 x 64 and 32 x 32 (us a rank's products
+// at N / P): 516 / 4 26.5 / 17.7 / 13.5, 1080 / 8 49 / 32.1 / 24.4, 1124 / 4 (324 tiles of 32 x
+// 32) 49 / 29.1 / 31.3, 2000 / 8 84 / 49.7 / 53.5, 1784 / 4 75.1 / 70.8 / 76.6.
 int gemm_tile(int64_t m, int64_t n) {
   int best = 0;
   double cost = -1.0;
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < 5; ++i) {
     const double tiles = (double)((m + kTiles[i].m - 1) / kTiles[i].m) *
                          (double)((n + kTiles[i].n - 1) / kTiles[i].n);
     const double most = std::ceil(tiles / 256.0);
@@ -632,6 +635,10 @@ int gemm_run(int64_t m, int64_t n, int64_t k, int parts, int first, const double
     kernel = parts > 1 ? gemm_pair_kernel<32, 64, 16, 16, 32, true>
                        : gemm_pair_kernel<32, 64, 16, 16, 32, false>;
     threads = 512;
+  } else if (tile == 4) {
+    kernel = parts > 1 ? gemm_pair_kernel<32, 32, 16, 16, 32, true>
+                       : gemm_pair_kernel<32, 32, 16, 16, 32, false>;
+    threads = 256;
   }
   hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, s, g);
   return check_hip(hipGetLastError(), who);
@@ -665,7 +672,7 @@ extern "C" int fd_cannon_rank_f64(int64_t n, int32_t parts, int32_t rank, const 
     if (rc) return rc;
   }
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  // one launch for all products in 64 x 64 and 32 x 64 tiles, from ns = 32 on (a part's
+  // one launch for all products in tiles of 64 x 64 and less, from ns = 32 on (a part's
   // first stage is read whole) and up to kPartsTiles: with more tiles, blocks in
   // different parts of K share less of the B panels in L2
   if (ns >= 32 && gemm_offsets_fit(lda, ldb) && one_launch_pays(ns, n))

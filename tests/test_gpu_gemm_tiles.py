@@ -30,8 +30,8 @@ def _check(m, n, k, accumulate, pad=(3, 5, 2)):
     assert bool(torch.isnan(c[:, n:]).all())  # nothing outside C is written
 
 
-# 32 x 64 tiles (stages of 32), 64 x 64 and 128 x 128 (stages of 16)
-@pytest.mark.parametrize("m,n", [(33, 65), (31, 63), (511, 4090), (2045, 2047)])
+# 32 x 32 and 32 x 64 tiles (stages of 32), 64 x 64 and 128 x 128 (stages of 16)
+@pytest.mark.parametrize("m,n", [(33, 65), (31, 31), (65, 4095), (511, 4090), (2045, 2047)])
 @pytest.mark.parametrize("k", [1, 2, 15, 16, 17, 31, 32, 33, 47, 64, 97])
 def test_pair_kernel_tiles(m, n, k):
     _check(m, n, k, accumulate=k % 2 == 1)
@@ -47,11 +47,11 @@ def test_large_leading_dimension(ld):  # 64-bit offsets, and the last 32-bit one
     _check(3, 70, 37, True, pad=(ld - 37, 5, 2))
 
 
-# several products in one launch (64 x 64 and 32 x 64 tiles; stages of a product that are
-# whole, ragged and, at 32, single) and in several (the larger tiles: 128 x 128 at 4400,
-# 256 x 128 at 6146), in the ring order from any rank
+# several products in one launch (tiles of 64 x 64 at 4096, 32 x 64 at 1124, 32 x 32; stages of a product that are
+# whole, ragged and, at 32, single) and in several (the larger tiles, at 4400 and 6146), in
+# the ring order from any rank
 @pytest.mark.parametrize("N,P,rank", [(64, 2, 1), (99, 3, 0), (160, 5, 3), (185, 5, 4), (96, 4, 2),
-                                      (1026, 6, 5), (4096, 8, 7), (4400, 5, 1), (6146, 2, 1)])
+                                      (1026, 6, 5), (1124, 4, 3), (4096, 8, 7), (4400, 5, 1), (6146, 2, 1)])
 def test_cannon_launch_gives_the_bits_of_its_products(N, P, rank):
     ns = N // P
     g = torch.Generator(device="cuda").manual_seed(N + P)
