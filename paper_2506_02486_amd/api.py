@@ -463,9 +463,10 @@ def _run_struct(grid, u_prev, u, u_next, vdt2, sponge, nt, src, wavelet, rec_off
         r.src[0], r.src[1], r.src[2] = (int(x) for x in src)
     if rec_off is not None and rec_off.numel():
         if (rec_off.dtype != torch.int64 or traces is None or traces.dtype != torch.float32
+                or not rec_off.is_cuda or not traces.is_cuda or not rec_off.is_contiguous()
                 or not traces.is_contiguous() or traces.dim() != 2
                 or traces.shape[0] < nt or traces.shape[1] != rec_off.numel()):
-            raise TypeError(f"{who}: rec_off int64 and contiguous float32 traces "
+            raise TypeError(f"{who}: device int64 rec_off and contiguous device float32 traces "
                             "(>= nt, nrec)")
         r.nrec = rec_off.numel()
         r.rec_off = rec_off.data_ptr()

@@ -1,0 +1,41 @@
+"""Argument checks of the native loops that need no GPU: what a run is given is checked
+before anything is enqueued.  Only the checks run here, on host tensors."""
+import numpy as np
+import pytest
+import torch
+
+api = pytest.importorskip("paper_2506_02486_amd.api")
+
+
+class _Device(torch.Tensor):
+    """A host tensor that calls itself a device tensor (nothing reads it here)."""
+    is_cuda = True
+
+
+def _device(t):
+    return t.as_subclass(_Device)
+
+
+def _struct(rec_off, traces, plane=None, nt=5):
+    g = api.Grid(9, 8, 7)
+    vol = [_device(g.zeros("cpu")) for _ in range(4)]
+    return api._run_struct(g, *vol, None, nt, None, None, rec_off, traces, None, None, plane, "run")
+
+
+def test_traces_and_offsets_must_be_on_the_device():
+    off, tr = torch.arange(3), torch.zeros((5, 3))
+    assert _struct(_device(off), _device(tr))[0].nrec == 3
+    for o, t in ((off, _device(tr)), (_device(off), tr), (off, tr)):
+        with pytest.raises(TypeError):
+            _struct(o, t)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode", api.Simulation.MODES)
+def test_host_traces_are_refused(mode):
+    n = 24
+    rec = np.array([[3, 4, 5], [6, 4, 5]], np.int32)
+    sim = api.Simulation(np.full((n, n, n), 2000.0, np.float32), exchange="loopback",
+                         geom=api.Geometry(src=(9, 9, 9), rec=rec))
+    with pytest.raises(TypeError):
+        sim.run(4, traces=torch.zeros((4, 2)), mode=mode)
