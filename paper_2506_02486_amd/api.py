@@ -468,6 +468,8 @@ def _run_struct(grid, u_prev, u, u_next, vdt2, sponge, nt, src, wavelet, rec_off
                 or traces.shape[0] < nt or traces.shape[1] != rec_off.numel()):
             raise TypeError(f"{who}: device int64 rec_off and contiguous device float32 traces "
                             "(>= nt, nrec)")
+        if rec_plane is not None and rec_plane.nrec != rec_off.numel():
+            raise TypeError(f"{who}: rec_plane must be the plane map of the receivers of rec_off")
         r.nrec = rec_off.numel()
         r.rec_off = rec_off.data_ptr()
         r.traces = traces.data_ptr()
@@ -682,6 +684,17 @@ class Simulation:
         else:
             self.rec_off = None
             self.rec_plane = None
+
+    @property
+    def rec_off(self) -> torch.Tensor | None:
+        """Receiver offsets (``Grid.offsets``).  Assigning others drops ``rec_plane``, the
+        plane map of the old ones."""
+        return self._rec_off
+
+    @rec_off.setter
+    def rec_off(self, off: torch.Tensor | None):
+        self._rec_off = off
+        self.rec_plane = None
 
     @property
     def nrec(self) -> int:

@@ -30,6 +30,22 @@ def test_traces_and_offsets_must_be_on_the_device():
             _struct(o, t)
 
 
+def test_plane_map_must_be_that_of_the_receivers():
+    off, tr = _device(torch.arange(3)), _device(torch.zeros((5, 3)))
+    m = _device(torch.full((9 * 8,), -1, dtype=torch.int32))
+    assert _struct(off, tr, api.ReceiverPlane(m, 2, 3))[0].rec_k == 2
+    with pytest.raises(TypeError):
+        _struct(off, tr, api.ReceiverPlane(m, 2, 4))
+
+
+def test_other_receivers_drop_the_plane_map_of_the_old_ones():
+    sim = api.Simulation.__new__(api.Simulation)
+    sim.rec_off = torch.arange(3)
+    sim.rec_plane = api.ReceiverPlane(torch.zeros(1, dtype=torch.int32), 0, 3)
+    sim.rec_off = torch.arange(3)
+    assert sim.rec_plane is None and sim.nrec == 3
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("mode", api.Simulation.MODES)
 def test_host_traces_are_refused(mode):
