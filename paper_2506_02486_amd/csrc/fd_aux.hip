@@ -217,7 +217,8 @@ __global__ void __launch_bounds__(BS) scatter_add_kernel(float* a, const int64_t
 // edges 0.  v0 points at interior (0,0,0) of the input, which has its own strides.  A
 // wave takes an x row (64 points at a time) of one y in PREP_K planes, whose loads are
 // issued before any store, and a block of four waves four neighbouring y, so rows of any
-// length keep most lanes busy; a block goes on to every gridDim.z-th group of planes.
+// length keep most lanes busy (models of few, long rows: prep_launch); a block goes on to
+// every gridDim.z-th group of planes.
 // HBM-bound (one array read, one written); with a block of 256 points of one row the
 // padded rows of 264 points of a 256^3 grid gave every second block 8 points: 74.6 us,
 // now 36.1 (3.7 TB/s); 128^3 11.9 / 8.8, 384^3 187 / 156, 512^3 395 / 352.
@@ -276,13 +277,14 @@ __global__ void __launch_bounds__(BS) prep_vdt2_kernel(Geo g, const float* __res
                                                        long long vsy, long long vsz,
                                                        float* __restrict__ q, double dt,
                                                        bool from_m, int32_t* vm, int32_t* out) {
-  const int jj = (int)(blockIdx.y * PREP_Y + threadIdx.y) - 4;  // j in [-4, ny+4)
+  const int jj = (int)(blockIdx.y * blockDim.y + threadIdx.y) - 4;  // j in [-4, ny+4)
   const int oj = (jj < 0) + (jj >= g.ny);
   int mx = 0, mn = 0x7f800000;
   if (jj < g.ny + 4) {
     const int cj = wrap_index(jj, g.ny);
     for (int k0 = (int)blockIdx.z * PREP_K - 4; k0 < g.nz + 4; k0 += (int)gridDim.z * PREP_K) {
-      for (int ii = (int)threadIdx.x - 4; ii < g.nx + 4; ii += 64) {
+      for (int ii = (int)(blockIdx.x * blockDim.x + threadIdx.x) - 4; ii < g.nx + 4;
+           ii += (int)(gridDim.x * blockDim.x)) {
         const int oi = (ii < 0) + (ii >= g.nx);
         const int ci = wrap_index(ii, g.nx);
         float vin[PREP_K];
@@ -325,7 +327,7 @@ __global__ void __launch_bounds__(BS) prep_vdt2_kernel(Geo g, const float* __res
       // block (100 us)
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       const int done = __hip_atomic_fetch_add(vm + 2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (done == (int)(gridDim.y * gridDim.z) - 1) {
+      if (done == (int)(gridDim.x * gridDim.y * gridDim.z) - 1) {
         out[0] = __hip_atomic_load(vm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         out[1] = __hip_atomic_load(vm + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
@@ -346,18 +348,24 @@ __global__ void vmax_init_kernel(int32_t* out) {
 // an nx x ny x nz view.  A wave takes VMAX_LINES x-lines at a time (their row bases
 // are uniform: no per-element division), 64 points of each, so that a thread has
 // VMAX_LINES loads in flight; lines past the last repeat the last one (no effect on max
-// or min).  fd_cfl_dt, copy and synchronisation included, us before / after: 128^3 56 /
-// 40, 384^3 105 / 71, 512^3 167 / 122.
+// or min).  Few long lines are shared by `pieces` waves, which take every pieces-th 64
+// points.  fd_cfl_dt, copy and synchronisation included, us before / after: 128^3 56 / 40,
+// 384^3 105 / 71, 512^3 167 / 122; 2^20 x 1 x 1 (one wave / 256 blocks) 2351 / 40, 65536 x 8
+// x 8 382 / 39.
 constexpr int VMAX_LINES = 8;
 
 __global__ void __launch_bounds__(BS) vmax_kernel(int nx, int ny, int nz,
                                                   const float* __restrict__ v0, long long vsy,
-                                                  long long vsz, int32_t* out) {
+                                                  long long vsz, int pieces, int32_t* out) {
   const long long nline = (long long)ny * nz;
-  const long long wave = (long long)blockIdx.x * (BS / 64) + (threadIdx.x >> 6);
+  const int w = threadIdx.x >> 6;
+  // pieces > 1: the waves of a block and of gridDim.y blocks share the same lines
+  const bool shared = pieces > 1;
+  const long long wave = shared ? blockIdx.x : (long long)blockIdx.x * (BS / 64) + w;
+  const long long waves = shared ? gridDim.x : (long long)gridDim.x * (BS / 64);
+  const int piece = shared ? (int)blockIdx.y * (BS / 64) + w : 0;
   int mx = 0, mn = 0x7f800000;
-  for (long long l0 = wave * VMAX_LINES; l0 < nline;
-       l0 += (long long)gridDim.x * (BS / 64) * VMAX_LINES) {
+  for (long long l0 = wave * VMAX_LINES; l0 < nline; l0 += waves * VMAX_LINES) {
     const float* row[VMAX_LINES];
 #pragma unroll
     for (int u = 0; u < VMAX_LINES; ++u) {
@@ -365,7 +373,7 @@ __global__ void __launch_bounds__(BS) vmax_kernel(int nx, int ny, int nz,
       const long long k = line / ny;
       row[u] = v0 + k * vsz + (line - k * ny) * vsy;
     }
-    for (int i = threadIdx.x & 63; i < nx; i += 64) {
+    for (int i = piece * 64 + (threadIdx.x & 63); i < nx; i += pieces * 64) {
       int bits[VMAX_LINES];
 #pragma unroll
       for (int u = 0; u < VMAX_LINES; ++u) bits[u] = __float_as_int(row[u][i]);
@@ -542,25 +550,44 @@ hipError_t launch_scatter_add(float* a, const int64_t* off, const float* vals, i
   return hipGetLastError();
 }
 
-// Blocks of prep_vdt2_kernel: one per group of rows, or about `most`, each taking several
-// groups (the counter of VMAX takes the blocks one after the other).
-static dim3 prep_grid(const Geo& g, long long most) {
-  const unsigned by = (unsigned)((g.ny + 8 + PREP_Y - 1) / PREP_Y);
+// Grid and block of prep_vdt2_kernel: a block of four rows for each group of planes, or about
+// `most` blocks, each taking several groups (the counter of VMAX takes the blocks one after
+// the other).  Models of long rows for which those are fewer than 1024 blocks take 256
+// points of one row in a block, and share a row among as many blocks as make PREP_FILL.
+// us with the synchronisation, four rows a block / this: 2^20 x 1 x 1 15700 / 107, 65536 x 8
+// x 8 1451 / 39, 4096 x 64 x 2 69 / 25, 1000 x 100 x 100 46 / 36, 700 x 1 x 700 31 / 28.
+constexpr long long PREP_FILL = 4096;
+
+struct PrepLaunch {
+  dim3 grid, block;
+};
+
+static PrepLaunch prep_launch(const Geo& g, long long most) {
   const long long groups = (g.nz + 8 + PREP_K - 1) / PREP_K;
-  return dim3(1, by, (unsigned)std::min(groups, std::max(1LL, most / by)));
+  const unsigned by = (unsigned)((g.ny + 8 + PREP_Y - 1) / PREP_Y);
+  const long long bz = std::min(groups, std::max(1LL, most / by));
+  if (by * groups >= 1024 || g.nx + 8 < 2 * BS)
+    return {dim3(1, by, (unsigned)bz), dim3(64, PREP_Y)};
+  const unsigned rows = (unsigned)(g.ny + 8);
+  const long long rz = std::min(groups, std::max(1LL, most / rows));
+  const long long fill = std::max(1LL, std::min(most, PREP_FILL) / (rows * rz));
+  return {dim3((unsigned)std::min<long long>((g.nx + 8 + BS - 1) / BS, fill), rows, (unsigned)rz),
+          dim3(BS, 1)};
 }
 
 hipError_t launch_prepare_vdt2(const Geo& g, const float* v, float* q, double dt, bool from_m,
                                hipStream_t s) {
-  hipLaunchKernelGGL(prep_vdt2_kernel<false>, prep_grid(g, 1LL << 30), dim3(64, PREP_Y), 0, s, g,
-                     v + g.org, (long long)g.sy, (long long)g.sz, q, dt, from_m, nullptr, nullptr);
+  const PrepLaunch l = prep_launch(g, 1LL << 30);
+  hipLaunchKernelGGL(prep_vdt2_kernel<false>, l.grid, l.block, 0, s, g, v + g.org, (long long)g.sy,
+                     (long long)g.sz, q, dt, from_m, nullptr, nullptr);
   return hipGetLastError();
 }
 
 hipError_t launch_prepare_vdt2_max(const Geo& g, const float* v, long long vsy, long long vsz,
                                    float* q, double dt, int32_t* vm, int32_t* out, hipStream_t s) {
-  hipLaunchKernelGGL(prep_vdt2_kernel<true>, prep_grid(g, 512), dim3(64, PREP_Y), 0, s, g, v, vsy,
-                     vsz, q, dt, false, vm, out);
+  const PrepLaunch l = prep_launch(g, 512);
+  hipLaunchKernelGGL(prep_vdt2_kernel<true>, l.grid, l.block, 0, s, g, v, vsy, vsz, q, dt, false, vm,
+                     out);
   return hipGetLastError();
 }
 
@@ -601,10 +628,16 @@ hipError_t launch_vmax_view(int nx, int ny, int nz, const float* v, long long vs
   hipLaunchKernelGGL(vmax_init_kernel, dim3(1), dim3(64), 0, s, out);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const long long per = (long long)VMAX_LINES * (BS / 64);
-  const long long groups = ((long long)ny * nz + per - 1) / per;
-  const unsigned nb = (unsigned)std::min<long long>(std::max<long long>(groups, 1), 1024);
-  hipLaunchKernelGGL(vmax_kernel, dim3(nb), dim3(BS), 0, s, nx, ny, nz, v, vsy, vsz, out);
+  // one wave per VMAX_LINES lines; where that leaves fewer than VMAX_FILL blocks (models of
+  // few lines), a block's waves share them, and as many blocks as that takes
+  constexpr long long VMAX_FILL = 256;
+  const long long groups = ((long long)ny * nz + VMAX_LINES - 1) / VMAX_LINES;
+  const long long wide = (groups + BS / 64 - 1) / (BS / 64);
+  const long long share = std::min<long long>((nx + BS - 1) / BS, VMAX_FILL / groups);
+  const bool split = wide < VMAX_FILL && share > 1;
+  const dim3 nb((unsigned)std::min<long long>(split ? groups : wide, 1024), (unsigned)(split ? share : 1));
+  hipLaunchKernelGGL(vmax_kernel, nb, dim3(BS), 0, s, nx, ny, nz, v, vsy, vsz,
+                     split ? (int)share * (BS / 64) : 1, out);
   return hipGetLastError();
 }
 
