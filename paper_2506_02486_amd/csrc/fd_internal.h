@@ -220,9 +220,9 @@ hipError_t launch_grad_brick(const Geo& g, const Coef& c, const float* u, const 
 // The forward step (source and receiver row as launch_step's, rp->add false) that also
 // writes its stencil sum s_n = L u^n + f^n on the interior to keep; and the update of the
 // reverse sweep (u = b^{n+1}, up = b^{n+2}; rp, if given, with add) that also adds to g
-// the gradient terms up s2 (s2 may be NULL) and then u s1.  By bricks, or by the
-// 16-byte-lane kernel; same bits.  keep_fits: which arrays they take (strides and origin
-// multiples of 4 floats, arrays 16-byte aligned).
+// the gradient terms up s2 (s2 may be NULL) and then u s1.  By bricks, one thread per
+// point, or the 16-byte-lane kernel; same bits.  keep_fits: which arrays they take
+// (strides and origin multiples of 4 floats, arrays 16-byte aligned).
 bool keep_fits(const Geo& g, const float* const* arrays, int n);
 hipError_t launch_keep(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
                        const float* q, const float* ex, const float* ey, const float* ez,
@@ -236,6 +236,14 @@ hipError_t launch_keep_brick(const Geo& g, const Coef& c, const float* up, const
                              const float* ez, const fd_source* src, const RecPlane* rp,
                              float* keep, hipStream_t s);
 hipError_t launch_acc_brick(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
+                            const float* q, const float* ex, const float* ey, const float* ez,
+                            const RecPlane* rp, const float* s1, const float* s2, float* g_acc,
+                            hipStream_t s);
+hipError_t launch_keep_point(const Geo& g, const Coef& c, const float* up, const float* u,
+                             float* un, const float* q, const float* ex, const float* ey,
+                             const float* ez, const fd_source* src, const RecPlane* rp,
+                             float* keep, hipStream_t s);
+hipError_t launch_acc_point(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
                             const float* q, const float* ex, const float* ey, const float* ez,
                             const RecPlane* rp, const float* s1, const float* s2, float* g_acc,
                             hipStream_t s);

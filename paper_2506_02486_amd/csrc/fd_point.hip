@@ -25,15 +25,27 @@ struct PFaces {
   float* out[6];
 };
 
+// FWD: the update.  KEEP: the update, which also writes its stencil sum s_n = L u^n + f^n.
+// ACC: the update of the reverse sweep (u = b^{n+1}, up = b^{n+2}), which also adds the
+// gradient terms of the s it is given (why: fd_stencil4.hip).
+enum PointMode { P_FWD = 0, P_KEEP = 1, P_ACC = 2 };
+
+struct PGrad {
+  float* keep;
+  const float* s1;
+  const float* s2;
+  float* g_acc;
+};
+
 // REC: 1 writes the receiver row of plane rk, 2 adds the row scaled by
 // vdt2 / (1+eta) there (the scaled adjoint's residual), as the marching kernel does
-template <bool SPONGE, int REC, bool XCH>
+template <bool SPONGE, int REC, bool XCH, PointMode MODE = P_FWD>
 __global__ void __launch_bounds__(PX * PY)
     point_kernel(Geo g, Coef c, const float* up, const float* __restrict__ u, float* un,
                  const float* __restrict__ q, const float* __restrict__ ex,
                  const float* __restrict__ ey, const float* __restrict__ ez, int si, int sj, int sk,
                  float sw, const int32_t* __restrict__ rmap, int rk, float* __restrict__ rrow,
-                 PFaces fc) {
+                 PFaces fc, PGrad gr) {
   // up and un may be one array (two-array stepping): each thread reads its point of
   // up before it writes the same point of un, and touches no other point of either
   const int x = blockIdx.x * PX + threadIdx.x;
@@ -78,6 +90,18 @@ __global__ void __launch_bounds__(PX * PY)
   const float pa = up[o], pb = q[o];
   float eta = 0.f;
   if (SPONGE) eta = ex[x] + ey[y] + ez[k];
+  if (MODE == P_KEEP) {
+    // f is added where it is 0 too (that decides the sign of a zero)
+    float f = 0.f;
+    if (k == sk && x == si && y == sj) f = sw;
+    gr.keep[o] = lap + f;
+  }
+  if (MODE == P_ACC) {
+    float ga = gr.g_acc[o];
+    if (gr.s2) ga += pa * gr.s2[o];
+    ga += uc * gr.s1[o];
+    gr.g_acc[o] = ga;
+  }
   float v = 2.f * uc - pa + pb * lap;
   if (SPONGE && eta != 0.f) v = (v + eta * pa) * __builtin_amdgcn_rcpf(1.f + eta);
   if (k == sk && x == si && y == sj) {
@@ -138,7 +162,7 @@ hipError_t launch_step_point(const Geo& g, const Coef& c, const float* up, const
   const int variant = (ex ? 8 : 0) | (recm << 1) | (xch ? 1 : 0);
 #define FD_POINT(SP, RC, XC)                                                                   \
   hipLaunchKernelGGL((point_kernel<SP, RC, XC>), grid, dim3(PX, PY), 0, s, g, c, up, u, un, q, \
-                     ex, ey, ez, si, sj, sk, sw, map, rk, row, fc)
+                     ex, ey, ez, si, sj, sk, sw, map, rk, row, fc, PGrad{})
   switch (variant) {
     case 8 | 2 | 1: FD_POINT(true, 1, true); break;
     case 8 | 2: FD_POINT(true, 1, false); break;
@@ -153,6 +177,46 @@ hipError_t launch_step_point(const Geo& g, const Coef& c, const float* up, const
   }
 #undef FD_POINT
   return hipGetLastError();
+}
+
+namespace {
+
+template <PointMode MODE>
+hipError_t launch_point_grad(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
+                             const float* q, const float* ex, const float* ey, const float* ez,
+                             const fd_source* src, const RecPlane* rp, const PGrad& gr,
+                             hipStream_t s) {
+  constexpr int RC = MODE == P_KEEP ? 1 : 2;  // records, or adds the residual row
+  const dim3 grid((unsigned)((g.nx + PX - 1) / PX), (unsigned)((g.ny + PY - 1) / PY),
+                  (unsigned)g.nz);
+  const bool rec = rp && rp->map;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(PX, PY), 0, s, g, c, up, u, un, q, ex, ey, ez,
+                       src ? src->i : -1, src ? src->j : -1, src ? src->k : -1, src ? src->w : 0.f,
+                       rec ? rp->map : nullptr, rec ? rp->k : -1, rec ? rp->row : nullptr, PFaces{},
+                       gr);
+    return hipGetLastError();
+  };
+  if (ex) return rec ? launch(point_kernel<true, RC, false, MODE>) : launch(point_kernel<true, 0, false, MODE>);
+  return rec ? launch(point_kernel<false, RC, false, MODE>) : launch(point_kernel<false, 0, false, MODE>);
+}
+
+}  // namespace
+
+hipError_t launch_keep_point(const Geo& g, const Coef& c, const float* up, const float* u,
+                             float* un, const float* q, const float* ex, const float* ey,
+                             const float* ez, const fd_source* src, const RecPlane* rp, float* keep,
+                             hipStream_t s) {
+  return launch_point_grad<P_KEEP>(g, c, up, u, un, q, ex, ey, ez, src, rp,
+                                   PGrad{keep, nullptr, nullptr, nullptr}, s);
+}
+
+hipError_t launch_acc_point(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
+                            const float* q, const float* ex, const float* ey, const float* ez,
+                            const RecPlane* rp, const float* s1, const float* s2, float* g_acc,
+                            hipStream_t s) {
+  return launch_point_grad<P_ACC>(g, c, up, u, un, q, ex, ey, ez, nullptr, rp,
+                                  PGrad{nullptr, s1, s2, g_acc}, s);
 }
 
 }  // namespace fd

@@ -783,10 +783,32 @@ bool keep_fits(const Geo& g, const float* const* arrays, int n) {
   return true;
 }
 
+// Whether KEEP and ACC passes that are no bricks run one thread per point, where the plain
+// update does (point_kernel_pays: tile mode 3, else at most 2^22 points): models thin in y,
+// which leave most rows of a 32- or 64-row tile empty, and small ones.  us per step, KEEP
+// and ACC, 16-byte lanes / points: 700 x 1 x 700 29.5, 30.3 / 8.3, 8.9; 1000 x 4 x 1000 66.8,
+// 71.0 / 22.1, 25.6; 2000 x 1 x 2000 175, 190 / 39, 40; 12 x 200 x 200 16.9, 17.3 / 12.1,
+// 12.6; 14 x 300 x 300 (64-wide waves hold 5.8M) 30.7, 29.0 / 22.6, 27.2; 9 x 20 x 7 7.8, 8.1
+// / 4.3, 4.5.  Thin in x both leave most lanes empty and points are the slower: 4 x 400 x 400
+// (waves hold 10M, the tiles 11M) 36.5, 39.2 / 38.6, 45.9; 1 x 700 x 700 85, 89 / 149, 151.
+constexpr double kPointKeepLanes = 6e6;
+
+static bool keep_point_pays(const Geo& g) {
+  if (!point_kernel_pays(g)) return false;
+  if (tile_override() == 3) return true;
+  auto cover = [&](int tx, int ty) {
+    return (double)((g.nx + tx - 1) / tx * tx) * ((g.ny + ty - 1) / ty * ty) * g.nz;
+  };
+  const double lanes = cover(64, 1), tiles = wide_narrow_tiles(g) ? cover(64, 64) : cover(128, 32);
+  return lanes <= kPointKeepLanes || lanes <= 0.8 * tiles;
+}
+
 hipError_t launch_keep(const Geo& g, const Coef& c, const float* up, const float* u, float* un,
                        const float* q, const float* ex, const float* ey, const float* ez,
                        const fd_source* src, const RecPlane* rp, float* keep, hipStream_t s) {
   if (brick_grid(g)) return launch_keep_brick(g, c, up, u, un, q, ex, ey, ez, src, rp, keep, s);
+  if (keep_point_pays(g))
+    return launch_keep_point(g, c, up, u, un, q, ex, ey, ez, src, rp, keep, s);
   P4 p = wide_args(g, c, up, u, un, q, ex, ey, ez, src, rp);
   p.keep = keep;
   if (wide_narrow_tiles(g)) {
@@ -803,6 +825,8 @@ hipError_t launch_acc(const Geo& g, const Coef& c, const float* up, const float*
                       hipStream_t s) {
   if (brick_grid(g))
     return launch_acc_brick(g, c, up, u, un, q, ex, ey, ez, rp, s1, s2, g_acc, s);
+  if (keep_point_pays(g))
+    return launch_acc_point(g, c, up, u, un, q, ex, ey, ez, rp, s1, s2, g_acc, s);
   P4 p = wide_args(g, c, up, u, un, q, ex, ey, ez, nullptr, rp);
   p.s1 = s1;
   p.s2 = s2;

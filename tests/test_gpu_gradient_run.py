@@ -84,6 +84,38 @@ def test_runs_equal_per_step_calls(shape, tiles, nt, plane, sponge):
         api.set_tiles(0)
 
 
+# models thin in y or x, one thread per point in the automatic choice, and tile mode 3
+@pytest.mark.parametrize("shape,tiles", [((70, 1, 45), 0), ((131, 3, 64), 0), ((8, 70, 33), 0),
+                                         ((65, 17, 1), 0), ((2, 3, 1), 0), ((70, 37, 29), 3)])
+@pytest.mark.parametrize("nt,plane,sponge", [(5, True, True), (4, False, True), (1, True, False),
+                                             (2, True, False)])
+def test_runs_of_thin_models_equal_per_step_calls(shape, tiles, nt, plane, sponge):
+    test_runs_equal_per_step_calls(shape, tiles, nt, plane, sponge)
+
+
+def test_kept_sums_of_a_thin_model_cost_what_its_update_does():
+    """1000 x 4 x 1000: an update that also writes s_n takes the update's kernel (its floor
+    is 20 bytes a point against 16), not tiles that the model leaves mostly empty."""
+    g = api.Grid(1000, 4, 1000)
+    f = [g.zeros() for _ in range(3)]
+    q = g.zeros()
+    keep = [g.zeros() for _ in range(8)]
+
+    def best(run):
+        times = []
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            run()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    update = best(lambda: api.forward_run(g, *f, q, None, 8))
+    assert best(lambda: api.forward_keep(g, *f, q, None, 8, keep)) < 2 * update
+
+
 def test_refused_arguments():
     g = api.Grid(40, 20, 10)
     L = api.lib()
