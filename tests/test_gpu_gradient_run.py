@@ -93,6 +93,18 @@ def test_runs_of_thin_models_equal_per_step_calls(shape, tiles, nt, plane, spong
     test_runs_equal_per_step_calls(shape, tiles, nt, plane, sponge)
 
 
+def _best(run):
+    times = []
+    for _ in range(5):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        run()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b))
+    return min(times)
+
+
 def test_kept_sums_of_a_thin_model_cost_what_its_update_does():
     """1000 x 4 x 1000: an update that also writes s_n takes the update's kernel (its floor
     is 20 bytes a point against 16), not tiles that the model leaves mostly empty."""
@@ -100,20 +112,16 @@ def test_kept_sums_of_a_thin_model_cost_what_its_update_does():
     f = [g.zeros() for _ in range(3)]
     q = g.zeros()
     keep = [g.zeros() for _ in range(8)]
+    update = _best(lambda: api.forward_run(g, *f, q, None, 8))
+    assert _best(lambda: api.forward_keep(g, *f, q, None, 8, keep)) < 2 * update
 
-    def best(run):
-        times = []
-        for _ in range(5):
-            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-            a.record()
-            run()
-            b.record()
-            b.synchronize()
-            times.append(a.elapsed_time(b))
-        return min(times)
 
-    update = best(lambda: api.forward_run(g, *f, q, None, 8))
-    assert best(lambda: api.forward_keep(g, *f, q, None, 8, keep)) < 2 * update
+def test_pointwise_gradient_of_a_narrow_model_costs_less_than_its_update():
+    """4 x 400 x 400: g += D a s_n reads and writes 16 bytes a point and has no neighbours."""
+    g = api.Grid(4, 400, 400)
+    a, s, acc, out, q = (g.zeros() for _ in range(5))
+    step = _best(lambda: [api.adjoint_step(g, a, s, out, q) for _ in range(8)])
+    assert _best(lambda: [api.grad_accumulate(g, a, s, None, acc) for _ in range(8)]) < 0.5 * step
 
 
 def test_refused_arguments():
