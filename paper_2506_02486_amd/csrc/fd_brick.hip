@@ -30,7 +30,7 @@
 // us against 13.5).  One plane on grids of at most 2^20 points, which leave CUs idle
 // otherwise (80^3: 4.5 us against 4.8).  8 lanes (32 points, 128 threads) where 64-wide
 // bricks would cover a tenth more of the x extent than 32-wide ones, 16 lanes (64
-// points, 256 threads, fewer x halos) elsewhere: 192^3 20.1 us (16 lanes) against 20.6,
+// points, 256 threads, fewer x halos) elsewhere with two planes: 192^3 20.1 us (16 lanes) against 20.6,
 // 160^3 13.7 against 13.2, 224^3 32.4 against 30.9.
 //
 // Measured (us per step in the native loop, sponge 16, before / after; before: one
@@ -471,8 +471,13 @@ int brick_planes(long long points) { return points <= kOnePlanePoints ? 1 : 2; }
 int brick_planes(const Geo& g) { return brick_planes((long long)g.nx * g.ny * g.nz); }
 
 // 16 lanes (64 points) where 64-wide bricks cover at most a tenth more than 32-wide
-// ones (the figures are at the top of this file)
+// ones (the figures are at the top of this file).  One-plane bricks, whose grids leave CUs
+// idle, always 8: twice the blocks; us per step, 16 lanes / 8: 392 x 53 x 32 6.9 / 6.3 (one
+// thread per point 5.8-6.2), 64 x 64 x 200 5.0 / 4.5, 120 x 109 x 68 6.5 / 6.2, 128 x 64 x 64
+// 4.7 / 4.6; over 44 grids of 0.45 to 1 million points a mean of 1.05, the worst (36 x 90 x
+// 238) 0.97.
 int brick_lanes(const Geo& g) {
+  if (brick_planes(g) == 1) return 8;
   const int c64 = (g.nx + 63) / 64 * 64, c32 = (g.nx + 31) / 32 * 32;
   return 10 * c64 <= 11 * c32 ? 16 : 8;
 }
@@ -541,8 +546,7 @@ hipError_t launch_bricks(const BrickArgs& p, const BrickFaces& fc, int lanes, hi
   const dim3 grid((unsigned)nb), block((unsigned)(lanes * TROWS));
 #define FD_BRICK(L, K) \
   hipLaunchKernelGGL((brick_kernel<L, K, SPONGE, XCH, MODE, RADD>), grid, block, 0, s, p, fc)
-  if (lanes == 8 && kz == 1) FD_BRICK(8, 1);
-  else if (kz == 1) FD_BRICK(16, 1);
+  if (kz == 1) FD_BRICK(8, 1);  // (brick_lanes)
   else if (lanes == 8) FD_BRICK(8, 2);
   else FD_BRICK(16, 2);
 #undef FD_BRICK
