@@ -134,7 +134,8 @@ int fd_set_kchunk(int32_t kchunk);
  * as bricks (fd_step_bricks tells which): forward updates, fd_step_exchange /
  * fd_forward_run with all twelve face buffers (0.55 to 12.5 million points, nx a
  * multiple of 4; the faces then read and written in that one launch), and gradient
- * passes (up to 12.5 million points; small grids too); single updates (fd_step,
+ * passes (up to 12.5 million points, 8 million where nx is a multiple of 128; small
+ * grids too); single updates (fd_step,
  * fd_step_fused, fd_adjoint_step_scaled, and fd_step_exchange where nx is a multiple
  * of 128) of at most 2^22 points; strides, origin and buffers 16-byte
  * aligned.  Where bricks do not apply: a forward update that takes no faces inside

@@ -195,6 +195,15 @@ constexpr long long kBrickPointsMore = 12500000;
 // kBrickPointsMore, except where rows fill the 128-wide tiles of the kernel it replaces:
 // 512 x 128 x 128 38.9 / 36.0.)
 constexpr long long kBrickPointsOnce = 1LL << 22;
+// Gradient passes (launch_grad: single calls, which alternate with updates and read
+// another u^n each) of grids whose rows fill the 128-wide tiles of the kernel they would
+// replace; of others up to kBrickPointsMore.  us per update and gradient pass of a reverse
+// sweep over 40 states, that kernel / bricks: 160^3 44.5 / 32.8, 192^3 55.0 / 53.0, 512 x 128 x
+// 128 58.4 / 59.0, 256 x 256 x 180 78.0 / 80.5, 336 x 150 x 174 64.7 / 65.0, 224^3 77.9 / 79.5,
+// 338 x 226 x 146 81.0 / 80.8, 300 x 200 x 200 89.5 / 85.1, 400 x 160 x 190 91.6 / 87.5.
+// With every array from memory 192^3 60.2 / 56.2, 200^3 69.3 / 69.3, 512 x 128 x 128 59.5 /
+// 61.9, 336 x 150 x 174 66.4 / 68.3; with the same arrays again and again all gain a tenth.
+constexpr long long kBrickPointsGrad = 8000000;
 // Whether bricks can step g at all: tile mode 0, at most `most` points and kBrickCover
 // covered, strides
 // and origin multiples of 4 floats, extents that fill the bricks.

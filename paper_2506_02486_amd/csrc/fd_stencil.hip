@@ -750,7 +750,9 @@ hipError_t launch_adjoint(const Geo& g, const Coef& c, const float* ann, const f
 hipError_t launch_grad(const Geo& g, const Coef& c, const float* u, const float* an1,
                        float* gq, const float* ex, const float* ey, const float* ez,
                        const fd_source* src, hipStream_t s) {
-  if (brick_grid(g) && !(((uintptr_t)u | (uintptr_t)an1 | (uintptr_t)gq) & 15u))
+  // rows that fill the 128-wide tiles: those from kBrickPointsGrad on
+  const long long most = g.nx % 128 == 0 ? kBrickPointsGrad : kBrickPointsMore;
+  if (brick_grid(g, most) && !(((uintptr_t)u | (uintptr_t)an1 | (uintptr_t)gq) & 15u))
     return launch_grad_brick(g, c, u, an1, gq, ex, ey, ez, src, s);
   if (forward_wide_tiles(g)) {
     const float* const arr[4] = {an1, u, gq, gq};

@@ -85,3 +85,28 @@ def test_brick_bits_equal_other_kernels(shape):
                 assert same_bits(x, y), (tiles, i)
     finally:
         api.set_tiles(0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(256, 250, 125), (256, 256, 125), (260, 250, 125)])
+def test_gradient_pass_on_both_sides_of_its_limit(shape):
+    """Rows that fill 128-wide tiles, up to and from 8 million points, and others: the
+    gradient pass gives the bits of the 64 x 32 tiles."""
+    g = api.Grid(*shape)
+
+    def field(seed):
+        t = g.zeros()
+        g.padded(t).copy_(torch.from_numpy(random_field((g.nz + 8, g.ny + 8, g.nx + 8), seed)))
+        return t
+
+    a, u, q = field(1), field(2), field(3)
+    acc = []
+    try:
+        for tiles in (0, 1):
+            api.set_tiles(tiles)
+            acc.append(field(4))
+            api.adjoint_step(g, None, a, g.zeros(), q, None, u_n=u, g_vdt2=acc[-1],
+                             src=((255, 4, 5), 0.7))
+    finally:
+        api.set_tiles(0)
+    assert same_bits(acc[0], acc[1])
