@@ -129,31 +129,33 @@ int fd_set_kchunk(int32_t kchunk);
 
 /* Performance knob: tile shape of the forward stencil kernels (fd_step,
  * fd_step_fused, fd_step_exchange, fd_forward_run, fd_adjoint_step_scaled):
- * 0 = automatic: grids of more than 0.45 million points (rows rounded up to 64)
- * and, in a run, at most 14.5 million (15.5 in whole bricks), whose arrays stay in cache between steps, run
- * as bricks (fd_step_bricks tells which): forward updates, fd_step_exchange /
+ * 0 = automatic: grids of more than 0.45 million points (rows rounded up to 64) and, in
+ * a run, at most 14.5 million (15.5 in whole bricks), whose arrays stay in cache between
+ * steps, run as bricks (fd_step_bricks tells which): forward updates, fd_step_exchange /
  * fd_forward_run with all twelve face buffers (0.55 to 12.5 million points, nx a
  * multiple of 4; the faces then read and written in that one launch), and gradient
  * passes (up to 12.5 million points, 8 million where nx is a multiple of 128; small
- * grids too); single updates (fd_step,
- * fd_step_fused, fd_adjoint_step_scaled, and fd_step_exchange where nx is a multiple
- * of 128) of at most 2^22 points; strides, origin and buffers 16-byte
- * aligned.  Where bricks do not apply: a forward update that takes no faces inside
- * the kernel -- fd_step, fd_step_fused, fd_forward_run without a second face set,
- * fd_adjoint_step_scaled(_res) -- runs one thread per point on grids of at most
- * 2^22 points, and so does fd_step_exchange / fd_forward_run with all twelve face
- * buffers on grids of at most 2^21 points, the faces then read and written in that
- * one launch; grids of at least 7.5 million points take the kernel of 16-byte lanes (the exchange form
- * where nx is a multiple of 128, with 128 x 32 tiles; the update without faces and
- * the gradient pass with 128 x 32 tiles, or 64 x 64 where the launch model prefers
- * them by a tenth, i.e. where a 128-wide tile column would be mostly empty; arrays
- * and face buffers 16-byte aligned); the others the z-marching kernel of one float
- * per lane, 64 x 16 tiles for grids of at most 2^20 points, 64 x 32 above.  1 =
+ * grids too); single updates (fd_step, fd_step_fused, fd_adjoint_step_scaled, and
+ * fd_step_exchange where nx is a multiple of 128) of at most 2^22 points; strides,
+ * origin and buffers 16-byte aligned.  Where bricks do not apply: a forward update that
+ * takes no faces inside the kernel -- fd_step, fd_step_fused, fd_forward_run without a
+ * second face set, fd_adjoint_step_scaled(_res) -- runs one thread per point on grids of
+ * at most 2^22 points, and so does fd_step_exchange / fd_forward_run with all twelve
+ * face buffers on grids of at most 2^21 points, the faces then read and written in that
+ * one launch; grids of at least 7.5 million points take the kernel of 16-byte lanes (the
+ * exchange form where nx is a multiple of 128, with 128 x 32 tiles; the update without
+ * faces and the gradient pass with 128 x 32 tiles, or 64 x 64 where the launch model
+ * prefers them by a tenth, i.e. where a 128-wide tile column would be mostly empty;
+ * arrays and face buffers 16-byte aligned); the others the z-marching kernel of one
+ * float per lane, 64 x 16 tiles for grids of at most 2^20 points, 64 x 32 above.  1 =
  * always 64 x 32, 2 = always 64 x 16 (both: never one thread per point, bricks nor
  * 16-byte lanes), 3 = one thread per point wherever it applies (64 x 16 elsewhere), 4 =
- * 16-byte lanes wherever they apply, 128 x 32 tiles (64 x 32 elsewhere), 5 = the
- * same with 64 x 64 tiles where the 16-byte-lane kernel takes no faces.
- * Process-wide; results do not depend on it (fd_step_kernel reports the choice).
+ * 16-byte lanes wherever they apply, 128 x 32 tiles (64 x 32 elsewhere), 5 = the same
+ * with 64 x 64 tiles where the 16-byte-lane kernel takes no faces.  (fd_forward_keep and
+ * fd_adjoint_run have no marching form of one float per lane: in mode 0 bricks or one
+ * thread per point where those pay, one thread per point in mode 3, else 16-byte lanes.)
+ * Process-wide; results do not depend on it (fd_step_bricks and fd_call_bricks report
+ * what runs as bricks, fd_step_kernel the kernel of what does not).
  * FD_EINVAL for another mode. */
 int fd_set_tiles(int32_t mode);
 
@@ -165,11 +167,12 @@ int fd_set_tiles(int32_t mode);
 int fd_step_launch(const fd_grid* g, int32_t out[4]);
 
 /* Which forward kernel a step over g takes where it does not run as bricks
- * (fd_step_bricks == 0, or arrays that bricks cannot take), as the next call would
- * choose it (process-wide fd_set_tiles mode included; volume arrays and face buffers
- * assumed 16-byte aligned, as torch allocates them): with_faces != 0 for
- * fd_step_exchange / fd_forward_run with all twelve face buffers, 0 for fd_step /
- * fd_step_fused / fd_forward_run without faces (no receiver row in the kernel).
+ * (fd_step_bricks == 0 for a run, fd_call_bricks == 0 for a single call, or arrays
+ * that bricks cannot take), as the next call would choose it (process-wide
+ * fd_set_tiles mode included; volume arrays and face buffers assumed 16-byte
+ * aligned, as torch allocates them): with_faces != 0 for fd_step_exchange /
+ * fd_forward_run with all twelve face buffers, 0 for fd_step / fd_step_fused /
+ * fd_forward_run without faces (no receiver row in the kernel).
  * out[0] = FD_KERNEL_*, out[1], out[2] = tile width and height in points (1 x 1:
  * one thread per point), out[3] = z planes per block, out[4] = z chunks, out[5] =
  * blocks (-1 for the one-thread-per-point kernel).  Host only; FD_EINVAL for a bad
@@ -186,6 +189,9 @@ int fd_step_kernel(const fd_grid* g, int32_t with_faces, int32_t out[6]);
  * aligned) runs as bricks, 0 if fd_step_kernel's kernel steps it; FD_EINVAL for a bad
  * grid.  Host only. */
 int fd_step_bricks(const fd_grid* g, int32_t with_faces);
+/* The same for a single call: fd_step, fd_step_fused or fd_adjoint_step_scaled(_res)
+ * (with_faces == 0), or fd_step_exchange with all twelve faces. */
+int fd_call_bricks(const fd_grid* g, int32_t with_faces);
 
 /* ----------------------------------------------------------- model prep
  * (set-up, step S0; not on the per-step path).  The paper names the acoustic

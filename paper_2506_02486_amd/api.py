@@ -400,10 +400,11 @@ def step_kernel(grid: Grid, faces: bool = False) -> dict:
             "blocks": nb}
 
 
-def step_bricks(grid: Grid, faces: bool = False) -> bool:
+def step_bricks(grid: Grid, faces: bool = False, once: bool = False) -> bool:
     """Whether a run's step over ``grid`` goes as bricks (fd_step_bricks): the grids that the
-    caches hold between steps."""
-    return bool(check(lib().fd_step_bricks(grid.ref, int(bool(faces))), "fd_step_bricks"))
+    caches hold between steps; with ``once``, whether a single call does (fd_call_bricks)."""
+    who = "fd_call_bricks" if once else "fd_step_bricks"
+    return bool(check(getattr(lib(), who)(grid.ref, int(bool(faces))), who))
 
 
 # ----------------------------------------------------------------- forward model

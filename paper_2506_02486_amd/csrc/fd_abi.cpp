@@ -99,6 +99,14 @@ bool overlaps(const fd_grid* g, const float* a, const float* b) {
   return a < b + n && b < a + n;
 }
 
+// Up to how many points a step runs as bricks (kBrickPoints... say why there), by whether
+// all twelve faces are in its launch and whether it is a single call or one of a run.  (A
+// single call with faces keeps the marching kernel where that one's 128-wide tiles are full.)
+long long brick_most(const Geo& geo, bool faces, bool once) {
+  if (faces) return once && geo.nx % 128 == 0 ? kBrickPointsOnce : kBrickPointsMore;
+  return once ? kBrickPointsOnce : kBrickPoints;
+}
+
 // The forward update with no faces inside the kernel: bricks or the one-thread-per-point
 // kernel on grids small enough to stay in cache, else the z-marching kernel (the
 // same bits whichever runs).  most: up to how many points bricks (kBrickPoints...).
@@ -266,7 +274,14 @@ int fd_step_bricks(const fd_grid* g, int32_t with_faces) {
   int rc = check_grid(g);
   if (rc) return rc;
   const Geo geo = make_geo(g);
-  return brick_step(geo, with_faces != 0, with_faces ? kBrickPointsMore : kBrickPoints);
+  return brick_step(geo, with_faces != 0, brick_most(geo, with_faces != 0, false));
+}
+
+int fd_call_bricks(const fd_grid* g, int32_t with_faces) {
+  int rc = check_grid(g);
+  if (rc) return rc;
+  const Geo geo = make_geo(g);
+  return brick_step(geo, with_faces != 0, brick_most(geo, with_faces != 0, true));
 }
 
 namespace {
@@ -488,9 +503,8 @@ static hipError_t step_exchange(const Geo& geo, const Coef& c, const float* up, 
   bool all12 = face_in && face_out;
   for (int f = 0; f < 6 && all12; ++f) all12 = face_in[f] && face_out[f];
   const float* const arrs[4] = {up, u, un, q};
-  // a single call keeps the marching kernel where its 128-wide tiles are full
-  const long long most = once && geo.nx % 128 == 0 ? kBrickPointsOnce : kBrickPointsMore;
-  const bool bricks = all12 && brick_takes(geo, arrs, most, face_in, face_out);
+  const bool bricks =
+      all12 && brick_takes(geo, arrs, brick_most(geo, true, once), face_in, face_out);
   if (bricks || (all12 && point_exchange_pays(geo))) {  // the whole step in one launch
     const RecPlane rp{rec_map, rec_k, row};
     const bool in_kernel = rec_map && nrec > 0;

@@ -36,6 +36,22 @@ def test_which_grids_run_as_bricks(shape, faces, want):
         api.set_tiles(0)
 
 
+@pytest.mark.parametrize("shape,faces,want", [
+    ((64, 64, 64), False, False), ((64, 128, 64), False, True), ((128, 256, 128), False, True),
+    ((128, 256, 129), False, False), ((256, 200, 150), False, False),
+    ((128, 256, 128), True, True), ((128, 256, 129), True, False), ((256, 136, 72), True, True),
+    ((132, 256, 129), True, True), ((260, 200, 150), True, True), ((225, 224, 224), True, False),
+    ((130, 130, 130), True, False)])
+def test_which_single_calls_run_as_bricks(shape, faces, want):
+    g = api.Grid(*shape)
+    assert api.step_bricks(g, faces, once=True) is want
+    api.set_tiles(1)
+    try:
+        assert api.step_bricks(g, faces, once=True) is False
+    finally:
+        api.set_tiles(0)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", SHAPES)
 def test_brick_bits_equal_other_kernels(shape):
