@@ -103,6 +103,20 @@ class FWIProblem:
                                         rec_plane=self.rec_plane)
         return traces
 
+    @property
+    def states(self) -> list[torch.Tensor]:
+        """The wavefields of the last ``forward`` with checkpoint_every = 0, stepped again
+        for each use (nt + 2 volumes): ``states[n]`` is u^n for n <= nt, the last is
+        u^{-1} = 0.  Empty where the forward sweep kept nothing."""
+        if not self.kept:
+            return []
+        g = self.grid
+        u = [g.zeros(self.device) for _ in range(self.nt + 2)]
+        for n in range(self.nt):
+            api.step_fused(g, u[n - 1], u[n], u[n + 1], self.vdt2, self.sponge,
+                           (self.src, float(self.w[n])))
+        return u
+
     # ------------------------------------------------------------ adjoint
     def backward(self, res: torch.Tensor, want_grad_w: bool = False, scaled: bool = True,
                  want_lambda_src: bool = False):

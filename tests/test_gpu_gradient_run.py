@@ -124,6 +124,25 @@ def test_pointwise_gradient_of_a_narrow_model_costs_less_than_its_update():
     assert _best(lambda: [api.grad_accumulate(g, a, s, None, acc) for _ in range(8)]) < 0.5 * step
 
 
+def test_states_of_a_kept_forward_run():
+    """FWIProblem.states: the wavefields whose stencil sums checkpoint_every = 0 keeps."""
+    from paper_2506_02486_amd.fwi import FWIProblem
+    nx, ny, nz, nt = 30, 22, 17, 6
+    rec = receivers_plane(nx, ny, 3)[::5]
+    p = FWIProblem((nx, ny, nz), 5e-4, (9, 8, 7), rec, nt, sponge_width=3, sponge_vmax=2500.0,
+                   checkpoint_every=0)
+    assert p.states == []
+    v = torch.from_numpy(smooth_velocity(nx, ny, nz, seed=2, sigma=3.0)).cuda()
+    tr = p.forward(1.0 / v.double().square().float())
+    u = p.states
+    assert len(u) == nt + 2 and not bool(u[0].any()) and not bool(u[-1].any())
+    for n in range(nt):
+        row = torch.zeros(len(rec), device="cuda")
+        api.record_receivers(p.grid, u[n + 1], p.rec_off, row)
+        assert same_bits(row, tr[n])
+    assert bool(tr.any())
+
+
 def test_refused_arguments():
     g = api.Grid(40, 20, 10)
     L = api.lib()
