@@ -22,6 +22,10 @@ runs it in lambda (``fd_adjoint_step``: lambda^n = 2 D lambda^{n+1} +
 L(vdt2 D lambda^{n+1}) - E D lambda^{n+2}, g += D lambda^{n+1} (L u^n + f^n),
 ``fd_scatter_add``, ``fd_grad_finalize``: grad_m = -g vdt2^2 / dt^2).
 
+Volumes held at once beside m and vdt2: with checkpoints every C steps, S segments, 2 (S - 1)
+checkpoints, C kept sums, three wavefields and three of the adjoint; with C = 0 nt kept sums
+and three more (unscaled four).
+
 dt and the sponge are fixed when the problem is built (they do not depend on m).
 All device work runs in libfd's kernels; torch allocates buffers and copies
 checkpoints.
@@ -64,7 +68,8 @@ class FWIProblem:
         self.src_off = torch.from_numpy(g.offsets(np.array([self.src], np.int32))).to(device)
         self.m = g.zeros(device)
         self.vdt2 = g.zeros(device)
-        self.ckpt: list[tuple[torch.Tensor, torch.Tensor]] = []
+        # (u^{s-1}, u^s) at the start of each interval; None: the zero state of the first
+        self.ckpt: list[tuple[torch.Tensor, torch.Tensor] | None] = []
         self.kept: list[torch.Tensor] = []  # checkpoint_every = 0: s_0 .. s_{nt-1}
 
     # ------------------------------------------------------------ forward
@@ -96,7 +101,7 @@ class FWIProblem:
         for s in range(0, self.nt, step):  # one native loop per checkpoint interval
             e = min(s + step, self.nt)
             if checkpoints:
-                self.ckpt.append((up.clone(), u.clone()))
+                self.ckpt.append((up.clone(), u.clone()) if s else None)
             up, u, un = api.forward_run(g, up, u, un, self.vdt2, self.sponge, e - s,
                                         src=self.src, wavelet=self.w[s:e],
                                         rec_off=self.rec_off, traces=traces[s:e],
@@ -175,8 +180,12 @@ class FWIProblem:
         for j in range(len(self.ckpt) - 1, -1, -1):
             s = j * self.C
             e = min(s + self.C, self.nt)
-            for f, c in zip(field, self.ckpt[j]):
-                f.copy_(c)
+            if self.ckpt[j] is None:
+                field[0].zero_()
+                field[1].zero_()
+            else:
+                field[0].copy_(self.ckpt[j][0])
+                field[1].copy_(self.ckpt[j][1])
             api.forward_keep(g, *field, self.vdt2, self.sponge, e - s, kept, src=self.src,
                              wavelet=self.w[s:e])
             yield s, e, kept

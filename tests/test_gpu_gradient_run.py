@@ -143,6 +143,34 @@ def test_states_of_a_kept_forward_run():
     assert bool(tr.any())
 
 
+@pytest.mark.parametrize("scaled", [True, False])
+@pytest.mark.parametrize("every,most", [(8, 2 * 3 + 8 + 6), (0, 32 + 3), (64, 32 + 6)])
+def test_volumes_a_gradient_holds(every, most, scaled):
+    """32 steps: a checkpointed gradient holds 2 (S - 1) + C + 6 volumes beside the model's
+    two (the zero state of the first segment is no checkpoint), a kept one nt + 3, or 4
+    unscaled."""
+    most += not scaled and every == 0
+    from paper_2506_02486_amd.fwi import FWIProblem
+    n, nt = 96, 32
+    rec = receivers_plane(n, n, 3)[::97]
+    p = FWIProblem((n, n, n), 5e-4, (9, 8, 7), rec, nt, sponge_width=3, sponge_vmax=2500.0,
+                   checkpoint_every=every)
+    m = torch.full((n, n, n), 1 / 2000.0 ** 2, device="cuda")
+    res = torch.zeros((nt, len(rec)), device="cuda")
+    grads = []
+    for _ in range(2):  # a second backward from the same checkpoints
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        if not grads:
+            res += p.forward(m)
+        grads.append(p.backward(res, scaled=scaled))
+        if len(grads) == 1:
+            peak = torch.cuda.max_memory_allocated() - before
+            assert peak < (most + 1) * 4 * p.grid.elems  # (the gradient returned: 0.5)
+    assert same_bits(*grads) and bool(grads[0].any())
+
+
 def test_refused_arguments():
     g = api.Grid(40, 20, 10)
     L = api.lib()
