@@ -36,6 +36,13 @@ def _ptr(t) -> int | None:
     return t.data_ptr()
 
 
+def _address(a: np.ndarray) -> int:
+    """Address of a host array (``a.ctypes.data`` costs a microsecond more)."""
+    if a.flags.writeable and a.flags.c_contiguous and a.size:
+        return C.addressof(C.c_char.from_buffer(a))
+    return a.ctypes.data
+
+
 class Grid:
     """One subdomain geometry (``fd_grid``): interior ``nx*ny*nz``, spacing ``d``."""
 
@@ -46,6 +53,7 @@ class Grid:
         self.d = tuple(float(x) for x in d)
         self.elems = check(lib().fd_grid_elems(C.byref(self.c)), "fd_grid_elems")
         self.ref = C.byref(self.c)
+        self._faces: tuple[int, ...] | None = None  # face_elems of each face, on first use
 
     @property
     def origin(self) -> int:
@@ -153,7 +161,7 @@ def ricker(nt: int, dt: float, f0: float = RICKER_F0, t0: float | None = None,
     if t0 is None:
         t0 = 1.0 / f0
     w = np.empty(max(nt, 1), dtype=np.float32)
-    check(lib().fd_ricker(w.ctypes.data, nt, n0, dt, f0, t0), "fd_ricker")
+    check(lib().fd_ricker(_address(w), nt, n0, dt, f0, t0), "fd_ricker")
     return w[:nt]
 
 
@@ -224,16 +232,19 @@ def _faces(faces, grid: Grid):
     float32 device tensor of at least that face's element count."""
     if len(faces) != 6:
         raise ValueError("expected six face buffers (-x, +x, -y, +y, -z, +z)")
-    arr = _lib._FACES()
-    for i in range(6):
+    if grid._faces is None:
+        grid._faces = tuple(grid.face_elems(i) for i in range(6))
+    ptrs = [None] * 6
+    for i, least in enumerate(grid._faces):
         f = faces[i]
-        if f is not None:
-            if (not isinstance(f, torch.Tensor) or f.dtype != torch.float32 or not f.is_cuda
-                    or not f.is_contiguous() or f.numel() < grid.face_elems(i)):
-                raise TypeError(f"face {i}: expected a contiguous float32 ROCm tensor of "
-                                f">= {grid.face_elems(i)} elements")
-        arr[i] = None if f is None else f.data_ptr()
-    return arr
+        if f is None:
+            continue
+        if (not isinstance(f, torch.Tensor) or f.dtype != torch.float32 or not f.is_cuda
+                or not f.is_contiguous() or f.numel() < least):
+            raise TypeError(f"face {i}: expected a contiguous float32 ROCm tensor of "
+                            f">= {least} elements")
+        ptrs[i] = f.data_ptr()
+    return _lib._FACES(*ptrs)
 
 
 def halo_pack(grid: Grid, u, faces, stream=None):
@@ -460,8 +471,8 @@ def _run_struct(grid, u_prev, u, u_next, vdt2, sponge, nt, src, wavelet, rec_off
         wa = np.ascontiguousarray(wavelet, dtype=np.float32)
         if wa.size < nt:
             raise ValueError(f"{who}: wavelet shorter than nt")
-        r.wavelet = wa.ctypes.data
-        r.src[0], r.src[1], r.src[2] = (int(x) for x in src)
+        r.wavelet = _address(wa)
+        r.src[:] = (int(src[0]), int(src[1]), int(src[2]))
     if rec_off is not None and rec_off.numel():
         if (rec_off.dtype != torch.int64 or traces is None or traces.dtype != torch.float32
                 or not rec_off.is_cuda or not traces.is_cuda or not rec_off.is_contiguous()
@@ -475,15 +486,11 @@ def _run_struct(grid, u_prev, u, u_next, vdt2, sponge, nt, src, wavelet, rec_off
         r.rec_off = rec_off.data_ptr()
         r.traces = traces.data_ptr()
     if send is not None:
-        fs = _faces(send, grid)
-        for f in range(6):
-            r.send[f] = fs[f]
+        r.send = _faces(send, grid)
     if send2 is not None:
         if send is None:
             raise ValueError(f"{who}: send2 needs send")
-        fs = _faces(send2, grid)
-        for f in range(6):
-            r.send2[f] = fs[f]
+        r.send2 = _faces(send2, grid)
     return r, bufs, wa
 
 

@@ -46,6 +46,30 @@ def test_other_receivers_drop_the_plane_map_of_the_old_ones():
     assert sim.rec_plane is None and sim.nrec == 3
 
 
+def test_host_side_of_a_step():
+    """Addresses of host arrays of every kind, and the faces' checks, made on each call
+    against sizes that a grid works out once."""
+    w = np.arange(4, dtype=np.float32)
+    fixed = w.copy()
+    fixed.flags.writeable = False
+    for a in (w, w[1:], fixed, np.empty(0, np.float32)):
+        assert api._address(a) == a.ctypes.data
+    g = api.Grid(9, 8, 7)
+    faces = [_device(f) for f in api.face_buffers(g, "cpu")]
+    faces[3] = None
+    for _ in range(2):
+        assert [p for p in api._faces(faces, g)] == [f if f is None else f.data_ptr()
+                                                     for f in faces]
+    for i in (0, 5):
+        bad = list(faces)
+        for f in (faces[i][:-1], faces[i].double(), torch.zeros(g.face_elems(i))):
+            bad[i] = f
+            with pytest.raises(TypeError):
+                api._faces(bad, g)
+    with pytest.raises(ValueError):
+        api._faces(faces[:5], g)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("mode", api.Simulation.MODES)
 def test_host_traces_are_refused(mode):
