@@ -37,6 +37,11 @@ import torch
 
 from . import api
 
+# checkpoint intervals up to which the scaled reverse sweep takes a segment's last step on
+# the wavefield itself (see _backward_scaled)
+DIRECT_STEPS = 4
+
+
 class FWIProblem:
     """One shot of an FWI gradient: geometry, time axis, source, receivers."""
 
@@ -148,12 +153,16 @@ class FWIProblem:
         api.scatter_add(g, B, self.rec_off, res[nt - 1])
         gq = g.zeros(self.device)
         lam_src = torch.zeros(nt, dtype=torch.float32, device=self.device) if want_lambda_src else None
-        for s, e, kept in self._segments():
+        for s, e, kept, last in self._segments(direct=True):
             for n in range(e - 1, s - 1, -1):
                 if lam_src is not None:
                     api.record_receivers(g, B, self.src_off, lam_src[n:n + 1])
-                api.grad_accumulate(g, B, kept[n - s], self.sponge, gq)
-                api.adjoint_step(g, A, B, A, self.vdt2, self.sponge)
+                if n == e - 1 and last is not None:
+                    api.adjoint_step(g, A, B, A, self.vdt2, self.sponge, u_n=last, g_vdt2=gq,
+                                     src=(self.src, float(self.w[n])))
+                else:
+                    api.grad_accumulate(g, B, kept[n - s], self.sponge, gq)
+                    api.adjoint_step(g, A, B, A, self.vdt2, self.sponge)
                 if n >= 1:
                     api.scatter_add(g, A, self.rec_off, res[n - 1])
                 A, B = B, A
@@ -164,31 +173,42 @@ class FWIProblem:
             return out, lam_src
         return out
 
-    def _segments(self):
-        """The segments of the reverse sweep, last first: (s, e, kept) with kept[i] =
-        s_{s+i} for s <= s + i < e, stored by the forward sweep or recomputed from the
-        segment's checkpoint (into the same volumes for every segment)."""
+    def _segments(self, direct: bool):
+        """The segments of the reverse sweep, last first: (s, e, kept, last).  kept[i] =
+        s_{s+i}, stored by the forward sweep or recomputed from the segment's checkpoint
+        (into the same volumes for every segment), for s <= s + i < e, last None; or with
+        ``direct`` for s + i < e - 1, and last = u^{e-1}, whose update is not needed."""
         if self.C == 0:
-            yield 0, self.nt, self.kept
+            yield 0, self.nt, self.kept, None
             return
         g = self.grid
         # only the interiors of the kept volumes are written and read; the wavefields'
         # zero halos are the Dirichlet boundary
         kept = [torch.empty(g.elems, dtype=torch.float32, device=self.device)
-                for _ in range(min(self.C, self.nt))]
-        field = [g.zeros(self.device) for _ in range(3)]
+                for _ in range(min(self.C, self.nt) - direct)]
+        field = [g.zeros(self.device) for _ in range(3 if len(kept) > 1 else len(kept))]
+        # a few steps one by one only read the checkpoint; more than one do that on large
+        # grids (a call costs 20 us of host time, copying the checkpoint 16 bytes a point)
+        single = 3 if g.elems > 1 << 22 else 1
         for j in range(len(self.ckpt) - 1, -1, -1):
             s = j * self.C
             e = min(s + self.C, self.nt)
-            if self.ckpt[j] is None:
-                field[0].zero_()
-                field[1].zero_()
+            n = e - s - direct
+            if n <= single:
+                up, u = self.ckpt[j] or (g.zeros(self.device), g.zeros(self.device))
+                for i in range(n):
+                    api.forward_keep(g, up, u, field[i], self.vdt2, self.sponge, 1, kept[i:i + 1],
+                                     src=self.src, wavelet=self.w[s + i:s + i + 1])
+                    up, u = u, field[i]
             else:
-                field[0].copy_(self.ckpt[j][0])
-                field[1].copy_(self.ckpt[j][1])
-            api.forward_keep(g, *field, self.vdt2, self.sponge, e - s, kept, src=self.src,
-                             wavelet=self.w[s:e])
-            yield s, e, kept
+                for i in range(2):
+                    if self.ckpt[j] is None:
+                        field[i].zero_()
+                    else:
+                        field[i].copy_(self.ckpt[j][i])
+                u = api.forward_keep(g, *field, self.vdt2, self.sponge, n, kept, src=self.src,
+                                     wavelet=self.w[s:s + n])[1]
+            yield s, e, kept, u if direct else None
 
     def _backward_scaled(self, res: torch.Tensor, want_grad_w: bool):
         g, nt = self.grid, self.nt
@@ -197,7 +217,22 @@ class FWIProblem:
         api.scatter_add_scaled(g, B, self.rec_off, res[nt - 1], self.vdt2, self.sponge)
         gb = g.zeros(self.device)
         grad_w = torch.zeros(nt, dtype=torch.float32, device=self.device) if want_grad_w else None
-        for s, e, kept in self._segments():
+        # a segment's last step on its state saves an update for two calls from here: worth it
+        # where segments are short (us over 10 steps at 64^3 and 256^3, so / not so: C = 1 517
+        # / 740 and 2425 / 3829, C = 2 485 / 507 and 2458 / 3014, C = 4 384 / 408 and 2373 / 2675)
+        for s, e, kept, last in self._segments(direct=self.C <= DIRECT_STEPS):
+            if last is not None:
+                e -= 1
+                if grad_w is not None:
+                    api.record_receivers(g, B, self.src_off, grad_w[e:e + 1])
+                inj = (self.rec_plane, res[e - 1]) if e and self.rec_plane is not None else None
+                api.adjoint_step_scaled(g, A, B, A, self.vdt2, self.sponge, u_n=last, g_b=gb,
+                                        src=(self.src, float(self.w[e])), res=inj)
+                if e and inj is None:
+                    api.scatter_add_scaled(g, A, self.rec_off, res[e - 1], self.vdt2, self.sponge)
+                A, B = B, A
+            if e == s:
+                continue
             A, B = api.adjoint_run(g, A, B, self.vdt2, self.sponge, e - s, kept, gb,
                                    rec_off=self.rec_off, res=res[s:e],
                                    res0=res[s - 1] if s >= 1 else None, rec_plane=self.rec_plane,

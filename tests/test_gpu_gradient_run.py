@@ -144,12 +144,12 @@ def test_states_of_a_kept_forward_run():
 
 
 @pytest.mark.parametrize("scaled", [True, False])
-@pytest.mark.parametrize("every,most", [(8, 2 * 3 + 8 + 6), (0, 32 + 3), (64, 32 + 6)])
+@pytest.mark.parametrize("every,most", [(8, 2 * 3 + 8 + 6), (1, 2 * 31 + 5), (3, 2 * 10 + 3 + 6), (0, 32 + 3), (64, 32 + 6)])
 def test_volumes_a_gradient_holds(every, most, scaled):
     """32 steps: a checkpointed gradient holds 2 (S - 1) + C + 6 volumes beside the model's
-    two (the zero state of the first segment is no checkpoint), a kept one nt + 3, or 4
-    unscaled."""
-    most += not scaled and every == 0
+    two (the zero state of the first segment is no checkpoint), a kept one nt + 3; unscaled
+    with C < 2 one more."""
+    most += not scaled and every < 2
     from paper_2506_02486_amd.fwi import FWIProblem
     n, nt = 96, 32
     rec = receivers_plane(n, n, 3)[::97]
@@ -169,6 +169,50 @@ def test_volumes_a_gradient_holds(every, most, scaled):
             peak = torch.cuda.max_memory_allocated() - before
             assert peak < (most + 1) * 4 * p.grid.elems  # (the gradient returned: 0.5)
     assert same_bits(*grads) and bool(grads[0].any())
+
+
+@pytest.mark.parametrize("shape", [(30, 22, 17), (180, 160, 130)])
+@pytest.mark.parametrize("plane", [True, False])
+def test_gradient_bits_of_every_checkpoint_interval(shape, plane):
+    """Segments of 1 step (no recomputation), of 2 to 4 (the last step on the state itself,
+    the others step by step or from a copied checkpoint), longer ones and shorter last
+    ones: the gradients of the kept run."""
+    from paper_2506_02486_amd.fwi import FWIProblem
+    nx, ny, nz = shape
+    nt = 11
+    rec = receivers_plane(nx, ny, 3)[::41]
+    if not plane:
+        rec[1::2, 2] = 5
+    m = 1.0 / torch.from_numpy(smooth_velocity(nx, ny, nz, seed=2, sigma=3.0)).cuda().square()
+    res = torch.from_numpy(random_field((nt, len(rec)), 4)).cuda()
+    want = {}
+    for every in (0, 1, 2, 3, 4, 5, 7, 10, 11, 64):
+        p = FWIProblem(shape, 5e-4, (9, 8, 7), rec, nt, sponge_width=3, sponge_vmax=6000.0,
+                       checkpoint_every=every)
+        p.forward(m)
+        for kw in ({"want_grad_w": True}, {"scaled": False, "want_lambda_src": True}):
+            got = p.backward(res, **kw)
+            for i, t in enumerate(got):
+                key = (i, *kw)
+                assert bool(t.any())
+                assert same_bits(want.setdefault(key, t), t), (every, key)
+
+
+def test_short_segments_recompute_nothing_that_is_not_needed():
+    """200^3, 12 steps: a checkpoint every step needs no recomputation and costs little more
+    than one every sixth."""
+    from paper_2506_02486_amd.fwi import FWIProblem
+    n, nt = 200, 12
+    rec = receivers_plane(n, n, 3)[::97]
+    m = torch.full((n, n, n), 1 / 2000.0 ** 2, device="cuda")
+    res = torch.zeros((nt, len(rec)), device="cuda")
+    cost = []
+    for every in (1, 6):
+        p = FWIProblem((n, n, n), 5e-4, (9, 8, 7), rec, nt, sponge_width=3, sponge_vmax=2500.0,
+                       checkpoint_every=every)
+        cost.append(_best(lambda: (p.forward(m), p.backward(res))))
+        del p
+    assert cost[0] < 1.4 * cost[1]
 
 
 def test_refused_arguments():
