@@ -639,6 +639,20 @@ void drop_prepared(Server* S, Shot* s) {
   drop_events(s);
 }
 
+// A shot whose steps and trace copy have ended (landed: without an error).  Its admission
+// work came before its steps, but a shot of few steps may have run them all before the
+// thread saw the end of that work: its stability is checked here then, and the resources
+// it still holds are given back.
+void drained_locked(Server* S, Shot* s, bool landed) {
+  if (landed && s->abort_code == FD_OK && s->check_pending) s->abort_code = check_vmax(s);
+  s->check_pending = false;
+  drop_prepared(S, s);
+  if (s->copied) (void)hipEventDestroy(s->copied);
+  s->copied = nullptr;
+  S->running--;
+  finish_locked(S, s, landed ? s->abort_code : FD_EDEVICE);
+}
+
 void progress(Server* S) {
   const hipError_t dev = hipSetDevice(S->device);
   std::unique_lock<std::mutex> lk(S->mu);
@@ -794,12 +808,7 @@ void progress(Server* S) {
       Shot* s = S->draining[i];
       const hipError_t q = hipEventQuery(s->copied);
       if (q == hipErrorNotReady) { ++i; continue; }
-      S->arena->release(s->off, s->L.total);
-      s->has_block = false;
-      (void)hipEventDestroy(s->copied);
-      s->copied = nullptr;
-      S->running--;
-      finish_locked(S, s, q != hipSuccess ? FD_EDEVICE : s->abort_code);
+      drained_locked(S, s, q == hipSuccess);
       S->draining.erase(S->draining.begin() + i);
       S->cv.notify_all();
     }
@@ -949,12 +958,7 @@ void stop_server(Server* S) {
     }
   for (Shot* s : S->draining) {  // copies ended in the final synchronisation
     const bool landed = s->copied && hipEventQuery(s->copied) == hipSuccess;
-    if (s->copied) (void)hipEventDestroy(s->copied);
-    s->copied = nullptr;
-    if (s->has_block) S->arena->release(s->off, s->L.total);
-    s->has_block = false;
-    S->running--;
-    finish_locked(S, s, landed ? s->abort_code : FD_EDEVICE);
+    drained_locked(S, s, landed);
   }
   S->draining.clear();
   S->stopped = true;

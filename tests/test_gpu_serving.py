@@ -320,3 +320,30 @@ def test_default_policy_runs_device_filling_grids_alone():
     assert sum(s.nt for s in mid) // 2 <= st["steps"] < sum(s.nt for s in mid)
     for s, r in zip(mid, res):
         assert same_bits(r[1], solo(s))
+
+
+def test_unstable_shot_that_ends_before_its_check(model):
+    """A shot of a few steps may have run them all before the server sees the maximum of its
+    velocity: it is still found unstable, and its staging buffers go back to the pool however
+    often that happens."""
+    import resource
+
+    v, _, dt, vmax = model
+    big = torch.full((400, 200, 250), vmax, device="cuda")
+    for width, vdesign in ((0, 0.0), (2, vmax)):
+        shots = [serving.Shot(big, 2, 1.2 * 0.45286 * 10.0 / vmax, (5, 5, 5),
+                              np.array([[1, 1, 1]], np.int32), sponge_width=width,
+                              sponge_vmax=vdesign),
+                 serving.Shot(big, 2, dt, (5, 5, 5), np.array([[1, 1, 1]], np.int32),
+                              sponge_width=width, sponge_vmax=vdesign)]
+        with serving.ShotServer(2 << 30, max_slots=2) as srv:
+            for _ in range(20):
+                ids = [srv.submit(s) for s in shots]
+                bad, good = [srv.wait(i) for i in ids]
+                assert bad[0] == _lib.FD_EINVAL and bad[1] is None
+                assert good[0] == _lib.FD_OK
+            before = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss
+            for _ in range(300):
+                srv.wait(srv.submit(shots[1]))
+            grown = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss - before
+            assert grown < 20 * 1024, f"{grown} KB"
