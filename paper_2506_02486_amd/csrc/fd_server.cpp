@@ -146,7 +146,7 @@ int layout_for(const fd_shot_desc* d, ShotLayout* L) {
   L->rmap = L->traces + align_up(4 * (size_t)d->nt * (size_t)std::max(d->nrec, 1));
   // receiver plane map (receivers on one z plane), nx * ny int32
   L->vm = L->rmap + (d->nrec > 0 ? align_up(4 * (size_t)d->nx * (size_t)d->ny) : 0);
-  L->total = L->vm + kAlign;  // two int32: max and min of v
+  L->total = L->vm + kAlign;  // three int32: max and min of v, blocks done
   int tx, ty;
   batch_tile_shape(&tx, &ty);
   const long long t = (long long)((d->nx + tx - 1) / tx) * ((d->ny + ty - 1) / ty) *
