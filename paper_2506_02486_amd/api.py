@@ -388,8 +388,8 @@ def set_tiles(mode: int):
 
 
 def step_launch(grid: Grid) -> dict:
-    """Launch shape of the z-marching forward kernel over ``grid`` (fd_step_launch); grids
-    of at most 2^22 points run fd_step and the fused forms one thread per point."""
+    """Launch shape of the one-float z-marching forward kernel over ``grid``
+    (fd_step_launch), where a step takes it (see ``step_kernel`` and ``step_bricks``)."""
     out = (C.c_int32 * 4)()
     check(lib().fd_step_launch(grid.ref, out), "fd_step_launch")
     tx, ty, kc, zc = out

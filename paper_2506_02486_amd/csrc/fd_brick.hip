@@ -30,8 +30,9 @@
 // us against 13.5).  One plane on grids of at most 2^20 points, which leave CUs idle
 // otherwise (80^3: 4.5 us against 4.8).  8 lanes (32 points, 128 threads) where 64-wide
 // bricks would cover a tenth more of the x extent than 32-wide ones, 16 lanes (64
-// points, 256 threads, fewer x halos) elsewhere with two planes: 192^3 20.1 us (16 lanes) against 20.6,
-// 160^3 13.7 against 13.2, 224^3 32.4 against 30.9.
+// points, 256 threads, fewer x halos) elsewhere with two planes: 192^3 20.1 us (16 lanes)
+// against 20.6, 160^3 13.7 against 13.2, 224^3 32.4 against 30.9.  Bricks of one plane are
+// 32 points wide (brick_lanes says why).
 //
 // Measured (us per step in the native loop, sponge 16, before / after; before: one
 // thread per point up to 160^3, 64 x 32 marching tiles at 192^3, 16-byte marching lanes

@@ -1,10 +1,10 @@
-// fd_point.hip -- the forward update of small grids, one thread per point.
+// fd_point.hip -- the forward update of small grids, one thread per point, and of larger
+// ones (up to 2^22 points) that bricks do not take.
 //
-// A grid of up to a few million points (the limits are in fd_launch.cpp) sits in
-// the L2 and MALL caches between steps, so its step is bound by latency rather than
-// bandwidth: the z-marching kernel's
-// blocks spend most of their life filling the nine-plane register queue of a short
-// chunk.  Here every thread reads its 25 stencil values directly (cache hits after
+// A grid of up to a few million points (the limits are in fd_launch.cpp and, against
+// bricks, in fd_internal.h) sits in the L2 and MALL caches between steps, so its step is
+// bound by latency rather than bandwidth: the z-marching kernel's blocks spend most of
+// their life filling the nine-plane register queue of a short chunk.  Here every thread reads its 25 stencil values directly (cache hits after
 // the first step) and writes its point, so the whole grid is in flight at once.
 // The arithmetic is that of the marching kernel, term for term and in the same
 // order (centre, x pairs, y pairs, z pairs; the damped form only where eta != 0;

@@ -82,22 +82,18 @@ constexpr int kAdmitStreams = 4;      // bound of the admission stream pool
 // 44.6 ms / 1.52x; 4.2M 0.996x / 40.9 ms / 1.42x; one shot at a time 0.995x / 41.0 ms /
 // 0.95x (plain: 39.8 ms).
 constexpr long long kFillPoints = 256LL * 128 * 32 * 8;
-// Under a backlog the running shots may hold up to this many points.  One launch of
-// two mid-size grids beats two launches (336 x 150 x 174 twice: 59.0 us against 2 x
-// 32.8; 256^3 twice: 90.6 against 2 x 47.8), of a large and a small grid it does not
-// (384^3 and 256^3: 222 us against 162 + 48).  Throughput at twice the plain loop's
-// rate on the 128..384^3 mix, with a cap on the running points at all steps (the same
-// box, three alternating runs each): 8.4M points 1.001x, 16.8M 1.004x, no co-running
-// 1.003x, against 0.999x for the fill with 25.2M under a backlog (before the 64 x 64
-// tiles for ragged grids, on another box: 8.4M 1.006x, 16.8M 1.009x, 25.2M 1.020x,
-// 33.6M 1.016x, 67.1M 0.916x).  Joining wherever the launch model (choose_kchunk's)
-// prices one launch of the running shots and the new one below the two launches apart
-// ran more shots together and gave 0.987x: the model overrates one launch of two large
-// grids.
-// Since mid-size grids run alone as bricks, in cache, they no longer gain from sharing a
-// launch of the 16-byte-lane kernel (two of 8M points: 59 us together, 2 x 23.7 apart):
-// 34.89 shots/s on the 128..384^3 mix with this limit, 35.32 with the 12.5M that are
-// stepped together as bricks.
+// Under a backlog the running shots may hold up to this many points: the documented
+// policy, from before mid-size grids ran as bricks, when one launch of two of them beat two
+// launches (336 x 150 x 174 twice: 59.0 us against 2 x 32.8; 256^3 twice: 90.6 against 2 x
+// 47.8; not of a large and a small grid: 384^3 and 256^3 222 us against 162 + 48) and the
+// 128..384^3 mix at twice the plain loop's rate ran at 1.004x the plain loop with it (8.4M
+// points 1.001x, no co-running 1.003x, 25.2M 0.999x; joining wherever the launch model
+// prices the shared launch below two 0.987x).
+// Two grids that run alone as bricks, in cache, no longer gain from it (59 us together, 2 x
+// 24.7 apart): the server runs that mix at 0.99x the plain loop, and with a limit of the
+// 12.5M points that are stepped together as bricks at 35.32 against 34.89 shots/s
+// (fd_server_set_admission sets one).  On the same arrivals both are faster than before
+// bricks: 34.0 against 31.5 shots/s at 70 a second, p99 108 against 116 ms at 16 a second.
 constexpr long long kBacklogPoints = 2 * kFillPoints;
 
 size_t align_up(size_t n) { return (n + kAlign - 1) / kAlign * kAlign; }
