@@ -403,23 +403,46 @@ __global__ void __launch_bounds__(BS) grad_finalize_kernel(Geo g, const float* g
   }
 }
 
-// g += D a s, as the gradient pass forms it from L u + f = s.  HBM-bound; a wave takes 64
-// points of a row and a block four rows.  us, a block to a row / this: 4 x 400 x 400 69.2 /
-// 21.9, 1 x 700 x 700 207 / 54, 300^3 139 / 96, 128^3 9.8 / 8.5, 256^3 41.9 / 42.4.
+// g += D a s, as the gradient pass forms it from L u + f = s.  HBM-bound (12 bytes read and
+// 4 written a point): a thread takes 4 points of a row (16-byte accesses where VEC: strides,
+// origin and arrays allow them), a block 64 points of 16 rows.  us, a block to a row and one
+// float per lane / this: 4 x 400 x 400 69.2 / 15.5, 1 x 700 x 700 207 / 32, 300^3 139 / 77,
+// 512 x 512 x 256 237 / 196 (5.5 TB/s), 128^3 9.8 / 7.4, 256^3 41.9 / 44.6 with the same
+// arrays again and again, a step of an unscaled reverse sweep there 243 / 234 (235 with the
+// gradient pass that it stands for).
+constexpr int ACC_X = 16;
+
+template <bool VEC>
 __global__ void __launch_bounds__(BS) grad_accumulate_kernel(Geo g, const float* __restrict__ a,
                                                              const float* __restrict__ sn,
                                                              const float* ex, const float* ey,
                                                              const float* ez,
                                                              float* __restrict__ gq) {
-  const int j = blockIdx.y * (BS / 64) + threadIdx.y;
+  const int j = blockIdx.y * (BS / ACC_X) + threadIdx.y;
   const int k = blockIdx.z;
   if (j >= g.ny) return;
-  for (int i = blockIdx.x * 64 + threadIdx.x; i < g.nx; i += gridDim.x * 64) {
-    const long long o = at(g, i, j, k);
-    const float eta = ex ? ex[i] + ey[j] + ez[k] : 0.f;
+  const float eyz = ex ? ey[j] : 0.f, ezk = ex ? ez[k] : 0.f;
+  auto term = [&](int i, float gv, float av, float sv) -> float {
+    const float eta = ex ? ex[i] + eyz + ezk : 0.f;
     float D = 1.f;
     if (eta != 0.f) D = __builtin_amdgcn_rcpf(1.f + eta);
-    gq[o] = gq[o] + D * a[o] * sn[o];
+    return gv + D * av * sv;
+  };
+  for (int i = 4 * (blockIdx.x * ACC_X + threadIdx.x); i < g.nx; i += 4 * gridDim.x * ACC_X) {
+    const long long o = at(g, i, j, k);
+    if (VEC && i + 4 <= g.nx) {
+      const float4 av = *reinterpret_cast<const float4*>(a + o);
+      const float4 sv = *reinterpret_cast<const float4*>(sn + o);
+      float4 gv = *reinterpret_cast<const float4*>(gq + o);
+      gv.x = term(i, gv.x, av.x, sv.x);
+      gv.y = term(i + 1, gv.y, av.y, sv.y);
+      gv.z = term(i + 2, gv.z, av.z, sv.z);
+      gv.w = term(i + 3, gv.w, av.w, sv.w);
+      *reinterpret_cast<float4*>(gq + o) = gv;
+    } else {
+      for (int e = 0; e < 4 && i + e < g.nx; ++e)
+        gq[o + e] = term(i + e, gq[o + e], a[o + e], sn[o + e]);
+    }
   }
 }
 
@@ -658,8 +681,15 @@ hipError_t launch_grad_finalize(const Geo& g, const float* gq, const float* q, d
 
 hipError_t launch_grad_accumulate(const Geo& g, const float* a, const float* sn, const float* ex,
                                   const float* ey, const float* ez, float* gq, hipStream_t s) {
-  const dim3 grid((unsigned)std::min((g.nx + 63) / 64, 256), (g.ny + BS / 64 - 1) / (BS / 64), g.nz);
-  hipLaunchKernelGGL(grad_accumulate_kernel, grid, dim3(64, BS / 64), 0, s, g, a, sn, ex, ey, ez, gq);
+  constexpr int rows = BS / ACC_X;
+  const dim3 grid((unsigned)std::min((g.nx + 63) / 64, 256), (g.ny + rows - 1) / rows, g.nz);
+  const float* const arr[3] = {a, sn, gq};
+  if (keep_fits(g, arr, 3))
+    hipLaunchKernelGGL(grad_accumulate_kernel<true>, grid, dim3(ACC_X, rows), 0, s, g, a, sn, ex, ey,
+                       ez, gq);
+  else
+    hipLaunchKernelGGL(grad_accumulate_kernel<false>, grid, dim3(ACC_X, rows), 0, s, g, a, sn, ex, ey,
+                       ez, gq);
   return hipGetLastError();
 }
 

@@ -116,6 +116,39 @@ def test_kept_sums_of_a_thin_model_cost_what_its_update_does():
     assert _best(lambda: api.forward_keep(g, *f, q, None, 8, keep)) < 2 * update
 
 
+@pytest.mark.parametrize("shape", [(64, 17, 3), (65, 16, 2), (66, 5, 4), (71, 33, 2), (3, 18, 5),
+                                   (1, 1, 1)])
+def test_pointwise_gradient_with_and_without_16_byte_accesses(shape):
+    """fd_grad_accumulate on arrays that 16-byte accesses can and cannot take: the same bits,
+    rows whose last float4 holds 1 to 4 points, nothing outside the interior written."""
+    g = api.Grid(*shape)
+    sp = api.Sponge(g, 2, 3000.0, 5e-4)
+    out = []
+    for off in (0, 1, 2):
+        a, s, acc = (torch.from_numpy(random_field((g.elems + off,), seed)).cuda()[off:]
+                     for seed in (1, 2, 3))
+        for t, seed in ((a, 1), (s, 2), (acc, 3)):
+            t.copy_(torch.from_numpy(random_field((g.elems,), seed)))
+        for sponge in (None, sp):
+            api.grad_accumulate(g, a, s, sponge, acc)
+        out.append(acc)
+    A, S, G = (g.interior(torch.from_numpy(random_field((g.elems,), i))).double().numpy()
+               for i in (1, 2, 3))
+    eta = (sp.eta_z.cpu().double().numpy()[:, None, None]
+           + sp.eta_y.cpu().double().numpy()[None, :, None]
+           + sp.eta_x.cpu().double().numpy()[None, None, :])
+    want = G + A * S + A * S / (1 + eta)
+    got = g.interior(out[0]).cpu().double().numpy()
+    # a few roundings of 2^-24 each, in D (v_rcp_f32: 1 ulp), its products and two sums
+    assert np.abs(got - want).max() <= 8 * 2.0 ** -24 * (np.abs(G) + 2 * np.abs(A * S)).max()
+    for t in out[1:]:
+        assert same_bits(t, out[0])
+    inside = torch.zeros(g.elems, dtype=torch.bool)
+    g.interior(inside).fill_(True)
+    before = torch.from_numpy(random_field((g.elems,), 3))
+    assert same_bits(out[0].cpu()[~inside], before[~inside])
+
+
 def test_pointwise_gradient_of_a_narrow_model_costs_less_than_its_update():
     """4 x 400 x 400: g += D a s_n reads and writes 16 bytes a point and has no neighbours."""
     g = api.Grid(4, 400, 400)
