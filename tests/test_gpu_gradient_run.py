@@ -232,10 +232,10 @@ def test_gradient_bits_of_every_checkpoint_interval(shape, plane):
 
 
 def test_short_segments_recompute_nothing_that_is_not_needed():
-    """200^3, 12 steps: a checkpoint every step needs no recomputation and costs little more
-    than one every sixth."""
+    """256^3, 12 steps: a checkpoint every step needs no recomputation and costs about what
+    one every sixth does."""
     from paper_2506_02486_amd.fwi import FWIProblem
-    n, nt = 200, 12
+    n, nt = 256, 12
     rec = receivers_plane(n, n, 3)[::97]
     m = torch.full((n, n, n), 1 / 2000.0 ** 2, device="cuda")
     res = torch.zeros((nt, len(rec)), device="cuda")
@@ -245,7 +245,7 @@ def test_short_segments_recompute_nothing_that_is_not_needed():
                        checkpoint_every=every)
         cost.append(_best(lambda: (p.forward(m), p.backward(res))))
         del p
-    assert cost[0] < 1.4 * cost[1]
+    assert cost[0] < 1.3 * cost[1]
 
 
 def test_refused_arguments():
